@@ -111,6 +111,31 @@ template <typename T>
 hipError_t launch_step(const StepParams &p, StateT<T> a, StateT<T> b,
                        StepRef ref, const QNode *qtab, hipStream_t s, bool b16 = false,
                        int ip = 0);
+// The step for few nodes (tpl_narrow.hip): bitwise launch_step with eight
+// Q-slices (p.qs == 8, no tile groups, two arrays).  It holds 16 nodes per
+// workgroup (4 for the FP64 form up to kNarrowSmall nodes, where 16 would
+// leave most CUs without a workgroup and the Q-disk does not fit one pass).
+//
+// Where it is the faster one (us per step, 64 nodes per wave / this kernel;
+// FP64, then FP32):
+//    1 x 256 NQ 16    97 / 24                  64^2 NQ 16   161 / 81,  91 / 42
+//    16^2 NQ 6        19 / 10                  64^2 NQ 6     21 / 14,  19 / 12
+//    80^2 NQ 16      190 / 142, 116 / 93       80^2 NQ 6     22 / 23,  20 / 19
+//    90^2 NQ 16      214 / 208, 142 / 121      96^2 NQ 6     25 / 31,  21 / 28
+//    110^2 NQ 16     249 / 312, 155 / 200     128^2 NQ 16   300 / 322, 149 / 242
+// that is up to 64 tiles of 64 nodes (256 workgroups, one per CU), and up to
+// 128 where the Q-disk is large enough that latency, not the second round of
+// workgroups, decides.
+constexpr int kNarrowSmall = 1024;
+inline bool use_narrow(int ntiles, int qs, int nqd) {
+  return qs == 8 && (ntiles <= 64 || (ntiles <= 128 && nqd > 64));
+}
+template <typename T>
+hipError_t launch_step_narrow(const StepParams &p, StateT<T> a, StateT<T> b, StepRef ref,
+                              const QNode *qtab, hipStream_t s, bool b16);
+template <typename T>
+hipError_t launch_step_batch_narrow(const InstDev *inst, int ninst, int nitems, int nqd,
+                                    int parity, hipStream_t s, bool shift, bool qe2);
 // Non-local spring term: S = kappa sum_Q Fhat [psi(r + Q/2) - psi(r - Q/2)]
 // of the read half's psi (bilinear interpolation, periodic) into its FLD
 // slots F_MXX (S_x) and F_MXY (S_y), where the step with p.shift reads it.
@@ -148,11 +173,11 @@ hipError_t launch_tile_dev(int planes, int nx, int ny, const double *col,
                            const float *ref, float *dst, hipStream_t s);
 // group > 1 (qs == 1 only): consecutive items per workgroup, one wave each.
 // ip = 1, 2: the in-place step kinds (every instance in place; qs == 1,
-// whole tiles), 0: two arrays.  qe2: every instance runs model (ii) (the
+// whole tiles), 0: two arrays.  nqd: the instances' largest.  qe2: every instance runs model (ii) (the
 // stress quasi-equilibria; not with shift).
 template <typename T>
 hipError_t launch_step_batch(const InstDev *inst, int ninst, int nitems, int qs, int grid,
-                             bool rowtile, int parity, hipStream_t s, int group = 1,
+                             bool rowtile, int parity, hipStream_t s, int nqd, int group = 1,
                              int ip = 0, bool shift = false, bool qe2 = false);
 // The shifted spring term's Q-sum for every item of a batch (before
 // launch_step_batch with shift; grid workgroups of eight waves walk the items).

@@ -8,140 +8,9 @@
 // T = double stores values; T = float stores deviations from an x-invariant
 // FP64 reference (the base state) and every kernel works on the full FP64
 // value ref + deviation.
-#include "tpl_internal.h"
-
-#include <type_traits>
+#include "tpl_step.h"
 
 namespace tplk {
-
-// ---------------------------------------------------------------------------
-// Velocity sets.
-// D2Q9 (Sec. VI.A; the standard set, the only one matching the weights
-// 4/9, 1/9, 1/36).
-constexpr int C9X[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
-constexpr int C9Y[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
-constexpr double W9[9] = {4.0 / 9,  1.0 / 9,  1.0 / 9,  1.0 / 9, 1.0 / 9,
-                          1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36};
-
-// D4Q25 (Sec. VI.B, Table I) as (v_x, v_y, Qdot_x, Qdot_y): the rest vector,
-// then for the coordinate pairs (vx,vy) (vx,Qx) (vx,Qy) (vy,Qx) (vy,Qy)
-// (Qx,Qy) the sign pairs (+,+) (+,-) (-,+) (-,-).
-constexpr int PV[25][4] = {
-    {0, 0, 0, 0},                                                    //
-    {1, 1, 0, 0},  {1, -1, 0, 0},  {-1, 1, 0, 0},  {-1, -1, 0, 0},   //
-    {1, 0, 1, 0},  {1, 0, -1, 0},  {-1, 0, 1, 0},  {-1, 0, -1, 0},   //
-    {1, 0, 0, 1},  {1, 0, 0, -1},  {-1, 0, 0, 1},  {-1, 0, 0, -1},   //
-    {0, 1, 1, 0},  {0, 1, -1, 0},  {0, -1, 1, 0},  {0, -1, -1, 0},   //
-    {0, 1, 0, 1},  {0, 1, 0, -1},  {0, -1, 0, 1},  {0, -1, 0, -1},   //
-    {0, 0, 1, 1},  {0, 0, 1, -1},  {0, 0, -1, 1},  {0, 0, -1, -1}};  //
-
-// D2Q9 direction of a D4Q25 velocity's r-part.
-__host__ __device__ constexpr int dir9(int vx, int vy) {
-  return (vx == 0 && vy == 0)    ? 0
-         : (vx == 1 && vy == 0)  ? 1
-         : (vx == 0 && vy == 1)  ? 2
-         : (vx == -1 && vy == 0) ? 3
-         : (vx == 0 && vy == -1) ? 4
-         : (vx == 1 && vy == 1)  ? 5
-         : (vx == -1 && vy == 1) ? 6
-         : (vx == -1 && vy == -1) ? 7
-                                  : 8;
-}
-__host__ __device__ constexpr int pdir(int k) { return dir9(PV[k][0], PV[k][1]); }
-// The velocity with the same r-part and reversed Q-part (Q bounce-back).
-__host__ __device__ constexpr int kstar(int k) {
-  int j = 0;
-  for (int i = 0; i < 25; ++i)
-    if (PV[i][0] == PV[k][0] && PV[i][1] == PV[k][1] &&
-        PV[i][2] == -PV[k][2] && PV[i][3] == -PV[k][3])
-      j = i;
-  return j;
-}
-static_assert(kstar(5) == 6 && kstar(21) == 24 && kstar(22) == 23 &&
-                  kstar(1) == 1 && pdir(9) == 1 && pdir(16) == 4,
-              "D4Q25 table");
-// Opposite velocities: -c_d (D2Q9) and -(v_k, Qdot_k) (D4Q25).
-__host__ __device__ constexpr int rev9(int d) {
-  return dir9(-C9X[d], -C9Y[d]);
-}
-__host__ __device__ constexpr int krev(int k) {
-  int j = 0;
-  for (int i = 0; i < 25; ++i)
-    if (PV[i][0] == -PV[k][0] && PV[i][1] == -PV[k][1] && PV[i][2] == -PV[k][2] &&
-        PV[i][3] == -PV[k][3])
-      j = i;
-  return j;
-}
-static_assert(rev9(1) == 3 && rev9(5) == 7 && rev9(8) == 6 && krev(0) == 0 && krev(1) == 4 &&
-                  krev(5) == 8 && krev(21) == 24 && krev(13) == 16,
-              "opposite velocities");
-
-__device__ __forceinline__ int xcd_tile(int bid, int tiles_per_xcd) {
-  // Workgroups are dispatched round-robin over the 8 XCDs; give each XCD a
-  // contiguous range of tiles so that stencil neighbours share its L2.
-  return tiles_per_xcd > 0 ? (bid & 7) * tiles_per_xcd + (bid >> 3) : bid;
-}
-
-// ---------------------------------------------------------------------------
-// Storage access.  Loads and stores at a wave-uniform plane base plus a 32-bit
-// byte offset (every offset is < sizeof(T) N < 2^32).  The base goes through
-// readfirstlane so that it stays in scalar registers; the compiler hoists the
-// zero-extended offsets out of the Q-loop and issues the accesses with 64-bit
-// per-lane addresses (SGPR base plus offset, one VALU add each).  Forcing the
-// SGPR-base instruction form instead (an opaque 32-bit offset per access)
-// saves 8-15 VGPRs but measured no faster: the step is bound by DRAM.
-template <typename T>
-__device__ __forceinline__ T *uni(T *p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<T *>(((uint64_t)hi << 32) | lo);
-}
-// Accesses go through the global address space explicitly: a generic
-// (flat) pointer would force 64-bit per-lane addresses and FLAT instructions.
-#define GLOBAL_AS __attribute__((address_space(1)))
-template <typename T>
-__device__ __forceinline__ T ldo(const T *base, uint32_t off) {
-  const char GLOBAL_AS *b = (const char GLOBAL_AS *)(base);
-  return *(const T GLOBAL_AS *)(b + off);
-}
-template <typename T>
-__device__ __forceinline__ void sto(T *base, uint32_t off, T v) {
-  char GLOBAL_AS *b = (char GLOBAL_AS *)(base);
-  *(T GLOBAL_AS *)(b + off) = v;
-}
-// Read-only tables (reference values, instance records) are read through the
-// constant address space, which the compiler turns into scalar loads whenever
-// the address is wave-uniform.
-#define CONSTANT_AS __attribute__((address_space(4)))
-template <typename T>
-__device__ __forceinline__ const T CONSTANT_AS *cst(const T *p) {
-  return (const T CONSTANT_AS *)(p);
-}
-
-// Full value from a stored one: identity for FP64, reference + deviation for
-// the FP32 form (ref = the plane's reference value at this row).
-__device__ __forceinline__ double full(double v, double) { return v; }
-__device__ __forceinline__ double full(float v, double ref) { return ref + (double)v; }
-template <typename T>
-__device__ __forceinline__ T stored(double v, double ref);
-template <>
-__device__ __forceinline__ double stored<double>(double v, double) { return v; }
-template <>
-__device__ __forceinline__ float stored<float>(double v, double ref) { return (float)(v - ref); }
-
-// BF16 form: a polymer population is stored as the BF16 rounding (nearest
-// even) of its deviation from the FP32 reference, the x-invariant base state;
-// solvent and psi keep FP32 deviations.  BF16 has FP32's exponent range, so
-// the deviations need no scaling.
-__device__ __forceinline__ uint16_t to_bf16(double v) {
-  uint32_t u = __float_as_uint((float)v);
-  u += 0x7fffu + ((u >> 16) & 1u);  // round to nearest even
-  return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ double from_bf16(uint16_t b) {
-  return (double)__uint_as_float(((uint32_t)b) << 16);
-}
 
 // ---------------------------------------------------------------------------
 // The fused step.  One lane per r-node; the Q-disk of that node is split over
@@ -162,65 +31,6 @@ __device__ __forceinline__ double from_bf16(uint16_t b) {
 // are wave-uniform (scalar loads).
 // One 64-node tile of one lattice (all qs slices of the workgroup take part).
 // red: LDS of qs * 12 * 64 doubles.
-// Non-local spring term: psi(r + Q/2) - psi(r - Q/2) of one Q-node's plane P
-// (stored T, FP32 reference rpq(row)) at node (x, y), each side by bilinear
-// interpolation between its four surrounding nodes, periodic.  The Q-node's
-// offsets are wave-uniform; the wrap loops run at most NQ/4 + 1 times (a
-// narrow lattice such as the one-column base-state run wraps more than once).
-__device__ __forceinline__ int wrap_to(int v, int n) {
-  while (v < 0) v += n;
-  while (v >= n) v -= n;
-  return v;
-}
-template <typename T, typename RefRow>
-__device__ __forceinline__ double spring_shift_diff(const T *P, int x, int y, int nx, int ny,
-                                                   double qx, double qy, RefRow rpq) {
-  const double ax = 0.5 * qx, ay = 0.5 * qy;
-  const double flx = floor(ax), fly = floor(ay);
-  const double fx = ax - flx, fy = ay - fly;
-  const int ix = (int)flx, iy = (int)fly;
-  auto at = [&](int xx, int yy) {
-    return full(ldo(P, (uint32_t)sizeof(T) * (uint32_t)(yy * nx + xx)), rpq(yy));
-  };
-  // + side: floor(Q/2) and the next node; - side: floor(-Q/2) = -floor(Q/2) - 1
-  // (Q/2 is never an integer: Q-nodes sit at half-integers), weights swapped
-  int xp0, xp1, yp0, yp1, xm0, xm1, ym0, ym1;
-  if ((ix < 0 ? -ix : ix) + 2 <= nx && (iy < 0 ? -iy : iy) + 2 <= ny) {
-    // offsets shorter than the lattice (wave-uniform test): every index lies
-    // in [-n, 2n), one conditional add or subtract wraps it
-    auto wr = [](int v, int n) {
-      v = v < 0 ? v + n : v;
-      return v >= n ? v - n : v;
-    };
-    xp0 = wr(x + ix, nx); xp1 = wr(x + ix + 1, nx);
-    yp0 = wr(y + iy, ny); yp1 = wr(y + iy + 1, ny);
-    xm0 = wr(x - ix - 1, nx); xm1 = wr(x - ix, nx);
-    ym0 = wr(y - iy - 1, ny); ym1 = wr(y - iy, ny);
-  } else {
-    xp0 = wrap_to(x + ix, nx); xp1 = wrap_to(x + ix + 1, nx);
-    yp0 = wrap_to(y + iy, ny); yp1 = wrap_to(y + iy + 1, ny);
-    xm0 = wrap_to(x - ix - 1, nx); xm1 = wrap_to(x - ix, nx);
-    ym0 = wrap_to(y - iy - 1, ny); ym1 = wrap_to(y - iy, ny);
-  }
-  const double vp = (1.0 - fx) * (1.0 - fy) * at(xp0, yp0) + fx * (1.0 - fy) * at(xp1, yp0) +
-                    (1.0 - fx) * fy * at(xp0, yp1) + fx * fy * at(xp1, yp1);
-  const double vm = fx * fy * at(xm0, ym0) + (1.0 - fx) * fy * at(xm1, ym0) +
-                    fx * (1.0 - fy) * at(xm0, ym1) + (1.0 - fx) * (1.0 - fy) * at(xm1, ym1);
-  return vp - vm;
-}
-
-// Mixture velocity: the velocity at which the momentum exchange of the two
-// species cancels (Sec. IV/V), from their g-momenta, the body force and the
-// Q-sum S of the spring term, weighted by 1 / (2 tJ + 1) per species.
-__device__ __forceinline__ void mixture_velocity(const StepParams &p, double rhoS, double JSx,
-                                                 double JSy, double rhoP, double JPx, double JPy,
-                                                 double Sx, double Sy, double Fbx, double Fby,
-                                                 double &Ux, double &Uy) {
-  const double den = rhoS * p.aS + rhoP * p.aP;
-  Ux = ((JSx + 0.5 * Fbx) * p.aS + (JPx + Sx / (2.0 * p.tJP)) * p.aP) / den;
-  Uy = ((JSy + 0.5 * Fby) * p.aS + (JPy + Sy / (2.0 * p.tJP)) * p.aP) / den;
-}
-
 // In-place streaming (IP != 0; one population array, a == b for XS and XP;
 // the AA pattern of Bailey et al., "Accelerating lattice Boltzmann fluid flow
 // simulations using graphics processors", ICPP 2009, with the Q-disk
@@ -325,58 +135,23 @@ __device__ __forceinline__ void step_tile(const StepParams &p, const StateT<T> &
   }
   // ---- mixture velocity: exchange of the two species cancels
   double Ux, Uy;
-  mixture_velocity(p, rhoS, JSx, JSy, rhoP, JPx, JPy, Sx, Sy, Fbx, Fby, Ux, Uy);
+  mixture_velocity(p, fma(rhoS, p.aS, rhoP * p.aP), JSx, JSy, JPx, JPy, Sx, Sy, Fbx, Fby, Ux,
+                   Uy);
   const bool writer = (slice == 0) && active;
 
   // ---- solvent collision (slice 0 writes)
   {
-    // model 1: f* about the species' own (inverted) momentum; model 2: f*
-    // with the equilibrium's momentum and the species' own (inverted) stress
-    const double vx = Ux + p.tJS * Fbx / rhoS, vy = Uy + p.tJS * Fby / rhoS;
-    const double v2 = vx * vx + vy * vy;
-    double usx = 0.0, usy = 0.0, Dxx = 0.0, Dxy = 0.0, Dyy = 0.0;
-    if constexpr (!QE2) {
-      usx = (2.0 * p.tJS * JSx + rhoS * Ux + p.tJS * Fbx) * p.aS / rhoS;
-      usy = (2.0 * p.tJS * JSy + rhoS * Uy + p.tJS * Fby) * p.aS / rhoS;
-    } else {
-      // P(f) - rho c_s^2 I with P(f) = (2 tau2 P(g) + rho (c_s^2 I + v v)) / (2 tau2 + 1)
-      double Pxx = 0.0, Pxy = 0.0, Pyy = 0.0;
-#pragma unroll
-      for (int d = 0; d < 9; ++d) {
-        if (C9X[d]) Pxx += gS[d];
-        if (C9Y[d]) Pyy += gS[d];
-        if (C9X[d] && C9Y[d]) Pxy += C9X[d] * C9Y[d] * gS[d];
-      }
-      const double t2 = 1.0 - p.pS;  // 2 tau2 / (2 tau2 + 1)
-      Dxx = t2 * Pxx + p.pS * rhoS * (1.0 / 3.0 + vx * vx) - rhoS / 3.0;
-      Dyy = t2 * Pyy + p.pS * rhoS * (1.0 / 3.0 + vy * vy) - rhoS / 3.0;
-      Dxy = t2 * Pxy + p.pS * rhoS * vx * vy;
-    }
-    const double us2 = usx * usx + usy * usy;
-    double jx = 0.0, jy = 0.0;
-#pragma unroll
-    for (int d = 0; d < 9; ++d) {
-      const double cv = C9X[d] * vx + C9Y[d] * vy;
-      const double fe = W9[d] * rhoS * (1.0 + 3.0 * cv + 4.5 * cv * cv - 1.5 * v2);
-      double fs;
-      if constexpr (!QE2) {
-        const double cu = C9X[d] * usx + C9Y[d] * usy;
-        fs = W9[d] * rhoS * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * us2);
-      } else {  // second-order Hermite form with the stress D + rho c_s^2 I
-        const double h = Dxx * (C9X[d] * C9X[d] - 1.0 / 3.0) +
-                         Dyy * (C9Y[d] * C9Y[d] - 1.0 / 3.0) + 2.0 * Dxy * C9X[d] * C9Y[d];
-        fs = W9[d] * (rhoS + 3.0 * rhoS * cv + 4.5 * h);
-      }
-      const double o = p.c1S * gS[d] + p.c2S * ((1.0 - p.rS) * fs + p.rS * fe);
-      if (C9X[d]) jx += C9X[d] * o;
-      if (C9Y[d]) jy += C9Y[d] * o;
-      if (writer) {
-        if constexpr (IP == 1)
-          sto(wplane(b.XS, rev9(d)), osrc[rev9(d)], stored<T>(o, rsd(rsstore, d)));
-        else
-          sto(wplane(b.XS, d), oR, stored<T>(o, rsd(rsstore, d)));
-      }
-    }
+    double jx, jy;
+    solvent_collide<QE2>(p, gS, rhoS, JSx, JSy, Ux, Uy, Fbx, Fby,
+                         [&](int d, double o) {
+                           if (!writer) return;
+                           if constexpr (IP == 1)
+                             sto(wplane(b.XS, rev9(d)), osrc[rev9(d)],
+                                 stored<T>(o, rsd(rsstore, d)));
+                           else
+                             sto(wplane(b.XS, d), oR, stored<T>(o, rsd(rsstore, d)));
+                         },
+                         jx, jy);
     if (writer) {
       sto(wfplane(b.FLD, F_JSX), fR, jx);
       sto(wfplane(b.FLD, F_JSY), fR, jy);
@@ -389,8 +164,6 @@ __device__ __forceinline__ void step_tile(const StepParams &p, const StateT<T> &
   for (int d = 0; d < 9; ++d) mg[d] = 0.0;
   double Mxx = 0.0, Mxy = 0.0, Myy = 0.0;
   const int nqd = p.nqd;
-  const double c2w0 = p.c2P * (1.0 / 3.0), c2w1 = p.c2P * (1.0 / 36.0);
-  const double one_r = 1.0 - p.rP;
   const bool qsync = (p.wg >> 16) & 1;  // only with qs == 1: equal trip counts
   for (int q = slice; q < nqd; q += p.qs) {
     if (qsync) __syncthreads();  // keep the group's waves on the same Q-node
@@ -433,24 +206,8 @@ __device__ __forceinline__ void step_tile(const StepParams &p, const StateT<T> &
       const uint32_t lo = ldo(uni(xp + (size_t)(25 * nqd + q) * N), oR >> 1);
       g[0] = __uint_as_float((hi << 16) | lo);
     }
-    double psi = 0.0, Jrx = 0.0, Jry = 0.0, JQx = 0.0, JQy = 0.0;
-    double P2[4][4] = {};  // model 2: second moments sum xi_a xi_b g (a <= b)
-#pragma unroll
-    for (int k = 0; k < 25; ++k) {
-      const double gk = G(k);
-      psi += gk;
-      if (PV[k][0]) Jrx += PV[k][0] * gk;
-      if (PV[k][1]) Jry += PV[k][1] * gk;
-      if (PV[k][2]) JQx += PV[k][2] * gk;
-      if (PV[k][3]) JQy += PV[k][3] * gk;
-      if constexpr (QE2) {
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int b2 = a; b2 < 4; ++b2)
-            if (PV[k][a] && PV[k][b2]) P2[a][b2] += PV[k][a] * PV[k][b2] * gk;
-      }
-    }
+    const PolyMoments<QE2> m = polymer_moments<QE2>(G);
+    const double psi = m.psi;
     // spring term: kappa Fhat (Q . grad psi^{n-1}), or with the shift
     // kappa Fhat [psi^{n-1}(r + Q/2) - psi^{n-1}(r - Q/2)]
     const T *P = plane(a.PSI, q);
@@ -460,68 +217,15 @@ __device__ __forceinline__ void step_tile(const StepParams &p, const StateT<T> &
     } else {
       const double pE = full(ldo(P, oE), rpq(y, q)), pW = full(ldo(P, oW), rpq(y, q));
       const double pN = full(ldo(P, oN), rpq(yp, q)), pS = full(ldo(P, oS), rpq(ym, q));
-      const double gx = 0.5 * (pE - pW), gy = 0.5 * (pN - pS);
-      qg = qn.qx * gx + qn.qy * gy;
+      qg = spring_taylor(qn.qx, qn.qy, pE, pW, pN, pS);
     }
     const double sx = p.kappa * qn.fx * qg, sy = p.kappa * qn.fy * qg;
-    // imposed fluxes and moment inversion
-    const double Erx = psi * Ux + sx, Ery = psi * Uy + sy;
-    const double EQx = psi * (Kxx * qn.qx + Kxy * qn.qy - p.DQ * qn.fx);
-    const double EQy = psi * (Kyx * qn.qx + Kyy * qn.qy - p.DQ * qn.fy);
-    double A[4];
-    if constexpr (!QE2) {
-      const double Frx = (2.0 * p.tJP * Jrx + Erx) * p.aP;
-      const double Fry = (2.0 * p.tJP * Jry + Ery) * p.aP;
-      const double FQx = (2.0 * p.tJP * JQx + EQx) * p.aP;
-      const double FQy = (2.0 * p.tJP * JQy + EQy) * p.aP;
-      // (1 - r) f* + r f_eq is the linear equilibrium of the blended fluxes
-      A[0] = 3.0 * c2w1 * (one_r * Frx + p.rP * Erx);
-      A[1] = 3.0 * c2w1 * (one_r * Fry + p.rP * Ery);
-      A[2] = 3.0 * c2w1 * (one_r * FQx + p.rP * EQx);
-      A[3] = 3.0 * c2w1 * (one_r * FQy + p.rP * EQy);
-    } else {
-      // f* and f_eq share the imposed fluxes; f* adds the Hermite term of
-      // D = P(f) - psi c_s^2 I, P(f) = (2 tau2 P(g) + psi c_s^2 I) / (2 tau2 + 1)
-      A[0] = 3.0 * c2w1 * Erx;
-      A[1] = 3.0 * c2w1 * Ery;
-      A[2] = 3.0 * c2w1 * EQx;
-      A[3] = 3.0 * c2w1 * EQy;
-      const double t2 = 1.0 - p.pP;
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        P2[a][a] = t2 * P2[a][a] + p.pP * psi / 3.0 - psi / 3.0;
-#pragma unroll
-        for (int b2 = a + 1; b2 < 4; ++b2) P2[a][b2] *= t2;
-      }
-    }
-    const double h = c2w1 * psi;
-    // model 2: the Hermite term's factor c2 (1 - r) 4.5 w_k, and -tr(D)/3
-    const double hw = 4.5 * one_r * c2w1;
-    const double trD3 = QE2 ? (P2[0][0] + P2[1][1] + P2[2][2] + P2[3][3]) / 3.0 : 0.0;
+    // imposed fluxes, moment inversion, blended equilibrium
+    const PolyTarget<QE2> target(p, m, Ux, Uy, Kxx, Kxy, Kyx, Kyy, sx, sy, qn.qx, qn.qy, qn.fx,
+                                 qn.fy);
 #pragma unroll
     for (int k = 0; k < 25; ++k) {
-      double t = (k == 0) ? c2w0 * psi : h;
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        if (PV[k][c]) t += PV[k][c] * A[c];
-      if constexpr (QE2) {
-        if (k == 0) {
-          t -= 4.5 * one_r * c2w0 * trD3;
-        } else {
-          // sum_ab D_ab (xi_a xi_b - delta_ab / 3) for xi with two unit entries
-          double hk = -trD3;
-#pragma unroll
-          for (int a = 0; a < 4; ++a)
-            if (PV[k][a]) {
-              hk += P2[a][a];
-#pragma unroll
-              for (int b2 = a + 1; b2 < 4; ++b2)
-                if (PV[k][b2]) hk += 2.0 * PV[k][a] * PV[k][b2] * P2[a][b2];
-            }
-          t += hw * hk;
-        }
-      }
-      const double go = p.c1P * G(k) + t;  // post-collision population
+      const double go = fma(p.c1P, G(k), target.term(k));  // post-collision population
       mg[pdir(k)] += go;
       if constexpr (B16) {
         // the deviation from the store reference; the rest population (k = 0)
@@ -576,9 +280,9 @@ __device__ __forceinline__ void step_tile(const StepParams &p, const StateT<T> &
             (uint16_t)(u0 & 0xffffu));
       }
     }
-    Mxx += psi * qn.qx * qn.fx;
-    Mxy += psi * qn.qx * qn.fy;
-    Myy += psi * qn.qy * qn.fy;
+    Mxx = fma(psi * qn.qx, qn.fx, Mxx);
+    Mxy = fma(psi * qn.qx, qn.fy, Mxy);
+    Myy = fma(psi * qn.qy, qn.fy, Myy);
   }
 
   // ---- combine the slices' partial sums
@@ -667,32 +371,9 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(3, 8)
     // uniform over the wave; over the workgroup too when group == 1, where
     // Q-slices synchronise (with group > 1 there is one slice and no barrier)
     if (item >= nitems) continue;
-    int lo = 0, hi = ninst - 1;    // last instance with item0 <= item
     const InstDev CONSTANT_AS *ci = cst(inst);  // read-only table: scalar loads
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (ci[mid].item0 <= item) lo = mid; else hi = mid - 1;
-    }
-    // Field-by-field reads through the constant address space keep every
-    // value in SGPRs (a whole-struct copy would go through private memory).
-    const InstDev CONSTANT_AS &d = ci[lo];
-    StepParams pp;
-#define TPL_LD(f) pp.f = d.p.f;
-    TPL_LD(nx) TPL_LD(ny) TPL_LD(nqd) TPL_LD(qs) TPL_LD(ntiles) TPL_LD(tiles_per_xcd)
-    TPL_LD(y0) TPL_LD(N) TPL_LD(aS) TPL_LD(aP) TPL_LD(tJS) TPL_LD(tJP) TPL_LD(c1S)
-    TPL_LD(c2S) TPL_LD(rS) TPL_LD(c1P) TPL_LD(c2P) TPL_LD(rP) TPL_LD(kappa) TPL_LD(DQ)
-    TPL_LD(F0) TPL_LD(kf) TPL_LD(src)
-#undef TPL_LD
-    pp.wg = 0;
-    pp.gate = nullptr;
-    pp.qe = QE2 ? 2 : 1;
-    pp.shift = 0;
-    if constexpr (QE2) {
-      pp.pS = d.p.pS;
-      pp.pP = d.p.pP;
-    } else {
-      pp.pS = pp.pP = 0.0;
-    }
+    const InstDev CONSTANT_AS &d = ci[batch_instance(ci, ninst, item)];
+    const StepParams pp = batch_params(d, QE2);
     const int rd = parity ^ d.cur0;
     const StateT<T> a{static_cast<T *>(d.XS[rd]), static_cast<T *>(d.XP[rd]),
                       static_cast<T *>(d.PSI[rd]), d.FLD[rd]};
@@ -706,9 +387,11 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(3, 8)
 
 template <typename T>
 hipError_t launch_step_batch(const InstDev *inst, int ninst, int nitems, int qs, int grid,
-                             bool rowtile, int parity, hipStream_t s, int group, int ip,
+                             bool rowtile, int parity, hipStream_t s, int nqd, int group, int ip,
                              bool shift, bool qe2) {
   if (group < 1 || (group > 1 && qs != 1) || qs * group > 8) return hipErrorInvalidValue;
+  if (use_narrow(nitems, qs, nqd) && ip == 0 && grid >= nitems)
+    return launch_step_batch_narrow<T>(inst, ninst, nitems, nqd, parity, s, shift, qe2);
   const size_t lds = qs > 1 ? (size_t)qs * 12 * 64 * sizeof(double) : 0;
   const int nunits = (nitems + group - 1) / group;
   const int per_xcd = (grid % 8 == 0 && nunits >= 64) ? (nunits + 7) / 8 : 0;
@@ -799,13 +482,15 @@ hipError_t launch_step_batch(const InstDev *inst, int ninst, int nitems, int qs,
   return hipGetLastError();
 }
 template hipError_t launch_step_batch<double>(const InstDev *, int, int, int, int, bool, int,
-                                              hipStream_t, int, int, bool, bool);
+                                              hipStream_t, int, int, int, bool, bool);
 template hipError_t launch_step_batch<float>(const InstDev *, int, int, int, int, bool, int,
-                                             hipStream_t, int, int, bool, bool);
+                                             hipStream_t, int, int, int, bool, bool);
 
 template <typename T>
 hipError_t launch_step(const StepParams &p, StateT<T> a, StateT<T> b,
                        StepRef r, const QNode *qtab, hipStream_t s, bool b16, int ip) {
+  if (use_narrow(p.ntiles, p.qs, p.nqd) && p.wg == 0 && ip == 0)
+    return launch_step_narrow<T>(p, a, b, r, qtab, s, b16);
   const int gsize = p.wg ? (p.wg & 255) * ((p.wg >> 8) & 255) : 1;
   const int grid = p.tiles_per_xcd > 0 ? 8 * p.tiles_per_xcd : p.ntiles / gsize;
   const size_t lds = p.qs > 1 ? (size_t)p.qs * 12 * 64 * sizeof(double) : 0;
@@ -1001,7 +686,9 @@ __device__ __forceinline__ void pre_u_node(const StepParams &p, const StateT<T> 
     Fby = p.src[N + r];
   }
   double Ux, Uy;
-  mixture_velocity(p, rhoS, JSx, JSy, rhoP, JPx, JPy, Sx, Sy, Fbx, Fby, Ux, Uy);
+  // which product is fused: as this pass always rounded it in either form
+  const double den = F32 ? fma(rhoP, p.aP, rhoS * p.aS) : fma(rhoS, p.aS, rhoP * p.aP);
+  mixture_velocity(p, den, JSx, JSy, JPx, JPy, Sx, Sy, Fbx, Fby, Ux, Uy);
   a.FLD[(size_t)F_UX * N + r] = Ux;
   a.FLD[(size_t)F_UY * N + r] = Uy;
 }
@@ -1032,15 +719,6 @@ __global__ void k_pre_u(StepParams p, StateT<T> a, const float *__restrict__ rsp
 // The same three passes over every item (64-node tile) of a batch; the read
 // half of each instance chosen by parity as in k_step_batch.  One wave per
 // item (and Q-node for the psi pass), items walked with the grid's stride.
-__device__ __forceinline__ int batch_instance(const InstDev CONSTANT_AS *ci, int ninst,
-                                              int item) {
-  int lo = 0, hi = ninst - 1;  // last instance with item0 <= item
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (ci[mid].item0 <= item) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
 template <typename T>
 __device__ __forceinline__ StateT<T> batch_half(const InstDev &d, int h) {
   return StateT<T>{static_cast<T *>(d.XS[h]), static_cast<T *>(d.XP[h]),

@@ -1873,9 +1873,9 @@ hipError_t batch_launch(const tpl_batch *b, int esize, int ninst, int nitems, in
                         bool rowtile, int parity, int group, bool inplace = true) {
   const int ip = (inplace && b->inplace) ? (((b->ip_odd + parity) & 1) ? 2 : 1) : 0;
   const bool sh = b->spring_shift != 0;  // base-state columns as well
+  int nqd = 1;  // Q-nodes per r-node, the largest of the instances
+  for (const tpl_ctx *x : b->inst) nqd = x->d.nqd > nqd ? x->d.nqd : nqd;
   if (b->gradients) {  // base-state columns as well
-    int nqd = 1;  // Q-nodes per r-node, the largest of the instances
-    for (const tpl_ctx *x : b->inst) nqd = x->d.nqd > nqd ? x->d.nqd : nqd;
     const hipError_t e =
         esize == 4 ? launch_same_step_fields_batch<float>(b->tab_d, ninst, nitems, nqd, parity, ip,
                                                           sh, b->stream)
@@ -1892,9 +1892,9 @@ hipError_t batch_launch(const tpl_batch *b, int esize, int ninst, int nitems, in
     if (e != hipSuccess) return e;
   }
   return esize == 4 ? launch_step_batch<float>(b->tab_d, ninst, nitems, qs, grid, rowtile, parity,
-                                               b->stream, group, ip, sh, b->qe2)
+                                               b->stream, nqd, group, ip, sh, b->qe2)
                     : launch_step_batch<double>(b->tab_d, ninst, nitems, qs, grid, rowtile,
-                                                parity, b->stream, group, ip, sh, b->qe2);
+                                                parity, b->stream, nqd, group, ip, sh, b->qe2);
 }
 
 // Enqueue n launches of the uploaded table with parities p0, p0^1, ...
