@@ -1089,56 +1089,116 @@ hipError_t launch_rest(int nqd, long long N, double rhoS0, double rhoP0,
 
 // Recompute every per-node field except U from the populations and psi of
 // the same half (used after any direct change of the state).
+//
+// One 64-node tile per workgroup, one wave per group of independent sums: the
+// marginal of r-direction 0 (five planes per Q-node), of directions 1-4 (four
+// each), of the four diagonals (one each), and M with the solvent's moments.
+// Each sum runs over the Q-nodes in order; kRefreshAhead Q-nodes' loads are in
+// flight at a time.  A thread per node (every sum in one chain) is bound by
+// load latency: 1280 us at 64^2 NQ 16, 1219 on a 64-row column and 531 at
+// 256^2 NQ 8, against 64, 75 and 181 here (2.7, 0.05 and 4.0 TB/s).
+constexpr int kRefreshWaves = 7, kRefreshAhead = 4;
 template <typename T>
-__global__ void k_refresh(int nqd, int nx, int ny, const QNode *__restrict__ qtab,
-                          StateT<T> a, RefView ref) {
+__global__ void __launch_bounds__(64 * kRefreshWaves)
+    k_refresh(int nqd, int nx, int ny, const QNode *__restrict__ qtab, StateT<T> a, RefView ref) {
+  __shared__ double mgs[9][64];
   const long long N = (long long)nx * ny;
-  const long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= N) return;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long long rr = (long long)blockIdx.x * 64 + lane;
+  const bool active = rr < N;
+  const long long r = active ? rr : N - 1;
   const int y = (int)(r / nx);
   constexpr bool F32 = std::is_same<T, float>::value;
   auto rv = [&](const float *tab, long long pl) { return F32 ? (double)tab[(size_t)pl * ny + y] : 0.0; };
-  double rs = 0.0, jx = 0.0, jy = 0.0;
-#pragma unroll
-  for (int d = 0; d < 9; ++d) {
-    const double v = full(a.XS[(size_t)d * N + r], rv(ref.XS, d));
-    rs += v;
-    jx += C9X[d] * v;
-    jy += C9Y[d] * v;
-  }
-  double mg[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-  double Mxx = 0.0, Mxy = 0.0, Myy = 0.0;
-  for (int q = 0; q < nqd; ++q) {
-#pragma unroll
-    for (int k = 0; k < 25; ++k) {
-      const long long pl = (long long)k * nqd + q;
-      mg[pdir(k)] += full(a.XP[(size_t)pl * N + r], rv(ref.XP, pl));
-    }
-    const double ps = full(a.PSI[(size_t)q * N + r], rv(ref.PSI, q));
-    Mxx += ps * qtab[q].qx * qtab[q].fx;
-    Mxy += ps * qtab[q].qx * qtab[q].fy;
-    Myy += ps * qtab[q].qy * qtab[q].fy;
-  }
-  double rp = 0.0;
-#pragma unroll
-  for (int d = 0; d < 9; ++d) rp += mg[d];
   double *G = a.FLD;
-  G[(size_t)F_RHOS * N + r] = rs;
-  G[(size_t)F_RHOP * N + r] = rp;
-  G[(size_t)F_JSX * N + r] = jx;
-  G[(size_t)F_JSY * N + r] = jy;
-  G[(size_t)F_MXX * N + r] = Mxx;
-  G[(size_t)F_MXY * N + r] = Mxy;
-  G[(size_t)F_MYY * N + r] = Myy;
+  // sums[s] += the stored values of plane(q, s), s < count, over all Q-nodes
+  auto walk = [&](const T *arr, const float *tab, auto count, auto plane, auto add) {
+    constexpr int S = decltype(count)::value;
+    T v[kRefreshAhead][S];
+    for (int q0 = 0; q0 < nqd; q0 += kRefreshAhead) {
 #pragma unroll
-  for (int d = 0; d < 9; ++d) G[(size_t)(F_M0 + d) * N + r] = mg[d];
+      for (int u = 0; u < kRefreshAhead; ++u)
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          v[u][s] = arr[(size_t)plane(q0 + u < nqd ? q0 + u : nqd - 1, s) * N + r];
+#pragma unroll
+      for (int u = 0; u < kRefreshAhead; ++u)
+        if (q0 + u < nqd)
+#pragma unroll
+          for (int s = 0; s < S; ++s) add(q0 + u, s, full(v[u][s], rv(tab, plane(q0 + u, s))));
+    }
+  };
+  auto marginal = [&](auto count, int first) {  // one r-direction: KDIR[first ...]
+    double m = 0.0;
+    walk(a.XP, ref.XP, count,
+         [&](int q, int s) { return (long long)KDIR[first + s] * nqd + q; },
+         [&](int, int, double v) { m += v; });
+    return m;
+  };
+  using One = std::integral_constant<int, 1>;
+  using Four = std::integral_constant<int, 4>;
+  using Five = std::integral_constant<int, 5>;
+  if (w == 0) {
+    mgs[0][lane] = marginal(Five{}, KDIR0[0]);
+  } else if (w == 1) {
+    mgs[1][lane] = marginal(Four{}, KDIR0[1]);
+  } else if (w == 2) {
+    mgs[2][lane] = marginal(Four{}, KDIR0[2]);
+  } else if (w == 3) {
+    mgs[3][lane] = marginal(Four{}, KDIR0[3]);
+  } else if (w == 4) {
+    mgs[4][lane] = marginal(Four{}, KDIR0[4]);
+  } else if (w == 5) {  // the diagonals: four sums of one plane each
+    double m[4] = {0.0, 0.0, 0.0, 0.0};
+    walk(a.XP, ref.XP, Four{},
+         [&](int q, int s) { return (long long)KDIR[KDIR0[5] + s] * nqd + q; },
+         [&](int, int s, double v) { m[s] += v; });
+#pragma unroll
+    for (int s = 0; s < 4; ++s) mgs[5 + s][lane] = m[s];
+  } else {
+    double Mxx = 0.0, Mxy = 0.0, Myy = 0.0;
+    walk(a.PSI, ref.PSI, One{}, [&](int q, int) { return (long long)q; },
+         [&](int q, int, double ps) {
+           const QNode CONSTANT_AS &qn = cst(qtab)[q];
+           Mxx = fma(ps * qn.qx, qn.fx, Mxx);
+           Mxy = fma(ps * qn.qx, qn.fy, Mxy);
+           Myy = fma(ps * qn.qy, qn.fy, Myy);
+         });
+    double rs = 0.0, jx = 0.0, jy = 0.0;
+#pragma unroll
+    for (int d = 0; d < 9; ++d) {
+      const double v = full(a.XS[(size_t)d * N + r], rv(ref.XS, d));
+      rs += v;
+      jx += C9X[d] * v;
+      jy += C9Y[d] * v;
+    }
+    if (active) {
+      G[(size_t)F_MXX * N + r] = Mxx;
+      G[(size_t)F_MXY * N + r] = Mxy;
+      G[(size_t)F_MYY * N + r] = Myy;
+      G[(size_t)F_RHOS * N + r] = rs;
+      G[(size_t)F_JSX * N + r] = jx;
+      G[(size_t)F_JSY * N + r] = jy;
+    }
+  }
+  __syncthreads();
+  if (w == 0 && active) {
+    double rp = 0.0;
+#pragma unroll
+    for (int d = 0; d < 9; ++d) {
+      rp += mgs[d][lane];
+      G[(size_t)(F_M0 + d) * N + r] = mgs[d][lane];
+    }
+    G[(size_t)F_RHOP * N + r] = rp;
+  }
 }
 
 template <typename T>
 hipError_t launch_refresh(int nqd, int nx, int ny, const QNode *qtab,
                           StateT<T> a, RefView ref, hipStream_t s) {
   const long long N = (long long)nx * ny;
-  hipLaunchKernelGGL(k_refresh<T>, dim3((unsigned)((N + 255) / 256)), dim3(256),
+  hipLaunchKernelGGL(k_refresh<T>, dim3((unsigned)((N + 63) / 64)), dim3(64 * kRefreshWaves),
                      0, s, nqd, nx, ny, qtab, a, ref);
   return hipGetLastError();
 }
@@ -1258,47 +1318,54 @@ hipError_t launch_perturb_field(int nx, int ny, int x0, int y0, int NX, int NY,
   return hipGetLastError();
 }
 
-// Add scale*du at first order to both species and to the lagged U.
+// Add scale*du at first order to both species and to the lagged U: one thread
+// per (node, Q-node), those of Q-node 0 the solvent and U too.  (A thread per
+// node walking the Q-disk took 1138 us at 64^2 NQ 16 and 5995 us at 72^2
+// NQ 32, against 46 and 292 here.)
 template <typename T>
 __global__ void k_perturb_apply(int nqd, int nx, int ny, const double *__restrict__ du,
                                 const double *__restrict__ scale, StateT<T> a,
                                 RefView ref) {
+#pragma clang fp contract(off)
   const long long N = (long long)nx * ny;
   const long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= N) return;
-  const int y = (int)(r / nx);
+  const int y = (int)(r / nx), q = blockIdx.y;
   constexpr bool F32 = std::is_same<T, float>::value;
   auto rv = [&](const float *tab, long long pl) { return F32 ? (double)tab[(size_t)pl * ny + y] : 0.0; };
   const double f = scale[0];
-  const double dx = f * du[r], dy = f * du[N + r];
-  double rs = 0.0;
+  const double u0 = du[r], dx = f * u0, dy = f * du[N + r];
+  // v . (dx, dy)
+  auto along = [&](int vx, int vy) {
+    return vx && vy ? fma(vx * f, u0, vy * dy) : vx ? vx * dx : vy * dy;
+  };
+  if (q == 0) {
+    double rs = 0.0;
 #pragma unroll
-  for (int d = 0; d < 9; ++d) rs += full(a.XS[(size_t)d * N + r], rv(ref.XS, d));
+    for (int d = 0; d < 9; ++d) rs += full(a.XS[(size_t)d * N + r], rv(ref.XS, d));
 #pragma unroll
-  for (int d = 0; d < 9; ++d) {
-    T &v = a.XS[(size_t)d * N + r];
-    v = stored<T>(full(v, rv(ref.XS, d)) + 3.0 * W9[d] * rs * (C9X[d] * dx + C9Y[d] * dy),
-                  rv(ref.XS, d));
-  }
-  for (int q = 0; q < nqd; ++q) {
-    double ps = 0.0;
-#pragma unroll
-    for (int k = 0; k < 25; ++k) {
-      const long long pl = (long long)k * nqd + q;
-      ps += full(a.XP[(size_t)pl * N + r], rv(ref.XP, pl));
+    for (int d = 0; d < 9; ++d) {
+      T &v = a.XS[(size_t)d * N + r];
+      v = stored<T>(fma(3.0 * W9[d] * rs, along(C9X[d], C9Y[d]), full(v, rv(ref.XS, d))),
+                    rv(ref.XS, d));
     }
-#pragma unroll
-    for (int k = 0; k < 25; ++k) {
-      if (PV[k][0] == 0 && PV[k][1] == 0) continue;
-      const long long pl = (long long)k * nqd + q;
-      T &v = a.XP[(size_t)pl * N + r];
-      v = stored<T>(full(v, rv(ref.XP, pl)) +
-                        3.0 * (1.0 / 36.0) * ps * (PV[k][0] * dx + PV[k][1] * dy),
-                    rv(ref.XP, pl));
-    }
+    a.FLD[(size_t)F_UX * N + r] += dx;
+    a.FLD[(size_t)F_UY * N + r] += dy;
   }
-  a.FLD[(size_t)F_UX * N + r] += dx;
-  a.FLD[(size_t)F_UY * N + r] += dy;
+  double g[25], ps = 0.0;
+#pragma unroll
+  for (int k = 0; k < 25; ++k) {
+    const long long pl = (long long)k * nqd + q;
+    g[k] = full(a.XP[(size_t)pl * N + r], rv(ref.XP, pl));
+    ps += g[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 25; ++k) {
+    if (PV[k][0] == 0 && PV[k][1] == 0) continue;
+    const long long pl = (long long)k * nqd + q;
+    a.XP[(size_t)pl * N + r] = stored<T>(
+        fma(3.0 * (1.0 / 36.0) * ps, along(PV[k][0], PV[k][1]), g[k]), rv(ref.XP, pl));
+  }
 }
 
 template <typename T>
@@ -1306,7 +1373,8 @@ hipError_t launch_perturb_apply(int nqd, int nx, int ny, const double *du,
                                 const double *scale, StateT<T> a, RefView ref,
                                 hipStream_t s) {
   const long long N = (long long)nx * ny;
-  hipLaunchKernelGGL(k_perturb_apply<T>, dim3((unsigned)((N + 255) / 256)),
+  if (nqd < 1 || nqd > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_perturb_apply<T>, dim3((unsigned)((N + 255) / 256), (unsigned)nqd),
                      dim3(256), 0, s, nqd, nx, ny, du, scale, a, ref);
   return hipGetLastError();
 }
