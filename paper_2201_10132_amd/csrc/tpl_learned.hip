@@ -20,6 +20,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 namespace tplk {
 
@@ -489,6 +490,7 @@ __global__ void k_source_drift(const double *__restrict__ F, const double *__res
 // Full-weighting restriction by an even factor m of planes of a fine
 // lattice (nxf x nyf) onto a coarse one: coarse (X, Y) averages fine
 // (m X + i, m Y + j), |i|, |j| <= m/2, weights 1/2 on the window's edges.
+// This form, one thread per coarse value, takes any factor.
 template <typename T>
 __global__ void k_restrict(int planes, int nxf, int nyf, int m, const T *__restrict__ src,
                            double *__restrict__ dst) {
@@ -514,6 +516,59 @@ __global__ void k_restrict(int planes, int nxf, int nyf, int m, const T *__restr
     acc += wy * row;
   }
   dst[(size_t)pl * Nc + rc] = acc / ((double)m * m);
+}
+
+// The same for m = 2 and 4, same sums in the same order.  Bound by the one
+// read of the fine planes, so every fine row is read once, in order: lane X
+// of a wave reads its M values of a row (and the M / 2 before them, its left
+// neighbour's, from the cache), and the wave walks kRestrictRows coarse rows
+// down, keeping the row sum that two coarse rows share.  The thread-per-value
+// form reads each fine row 1.25 times at stride M (1024^2 to 256^2, 1300
+// planes, with the refresh: 3.7 ms a call against 2.6; 5.0 TB/s).
+constexpr int kRestrictRows = 8;
+template <int M>
+__global__ void __launch_bounds__(256)
+    k_restrict_rows(int planes, int nxf, int nyf, const double *__restrict__ src,
+                    double *__restrict__ dst) {
+  constexpr int h = M / 2;
+  typedef double vm __attribute__((ext_vector_type(M)));
+  typedef double vh __attribute__((ext_vector_type(h)));
+  const int nxc = nxf / M, nyc = nyf / M;
+  const int X = blockIdx.x * 64 + (threadIdx.x & 63);
+  const int pl = blockIdx.z * 4 + (threadIdx.x >> 6);
+  if (pl >= planes || X >= nxc) return;
+  const double *P = src + (size_t)pl * nxf * nyf;
+  double *D = dst + (size_t)pl * nxc * nyc;
+  const int x0 = M * X, xl = X == 0 ? nxf - h : x0 - h;
+  // sum over the window's columns of fine row y
+  auto row = [&](int y) {
+    const vm v = *reinterpret_cast<const vm *>(P + (size_t)y * nxf + x0);
+    const vh l = *reinterpret_cast<const vh *>(P + (size_t)y * nxf + xl);
+    double lv[h], vv[M];
+    __builtin_memcpy(lv, &l, sizeof lv);
+    __builtin_memcpy(vv, &v, sizeof vv);
+    double s = 0.5 * lv[0];
+#pragma unroll
+    for (int i = 1; i < h; ++i) s += lv[i];
+#pragma unroll
+    for (int i = 0; i < h; ++i) s += vv[i];
+    return s + 0.5 * vv[h];
+  };
+  const int Y0 = blockIdx.y * kRestrictRows;
+  const int Y1 = Y0 + kRestrictRows < nyc ? Y0 + kRestrictRows : nyc;
+  double edge = row(Y0 == 0 ? nyf - h : M * Y0 - h);
+  for (int Y = Y0; Y < Y1; ++Y) {
+    double r[M];
+#pragma unroll
+    for (int j = 0; j < M; ++j) r[j] = row(M * Y - h + 1 + j < 0 ? M * Y - h + 1 + j + nyf
+                                                                  : M * Y - h + 1 + j);
+    double acc = 0.5 * edge;
+#pragma unroll
+    for (int j = 0; j < M - 1; ++j) acc += r[j];
+    edge = r[M - 1];
+    acc += 0.5 * edge;
+    D[(size_t)Y * nxc + X] = acc / (double)(M * M);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -744,6 +799,21 @@ template <typename T>
 hipError_t launch_restrict(int planes, int nxf, int nyf, int m, const T *src, double *dst,
                            hipStream_t s) {
   const long long n = (long long)(nxf / m) * (nyf / m) * planes;
+  const int nxc = nxf / m, nyc = nyf / m;
+  // rows of M doubles start 16-byte aligned if src does: nxf is a multiple of m
+  const bool rows = std::is_same<T, double>::value && (m == 2 || m == 4) &&
+                    reinterpret_cast<uintptr_t>(src) % (8 * m) == 0 && planes <= 4 * 65535;
+  if (rows) {
+    const dim3 grid((nxc + 63) / 64, (nyc + kRestrictRows - 1) / kRestrictRows, (planes + 3) / 4);
+    if (grid.y <= 65535) {
+      const double *p = reinterpret_cast<const double *>(src);
+      if (m == 4)
+        hipLaunchKernelGGL(k_restrict_rows<4>, grid, dim3(256), 0, s, planes, nxf, nyf, p, dst);
+      else
+        hipLaunchKernelGGL(k_restrict_rows<2>, grid, dim3(256), 0, s, planes, nxf, nyf, p, dst);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL(k_restrict<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, planes,
                      nxf, nyf, m, src, dst);
   return hipGetLastError();
