@@ -251,21 +251,25 @@ struct MlpDev {
   const float *out_mean, *out_std;
   int nin, nout;
 };
-// Floats of one wave's gradient record (see k_mlp_train).
+// Floats of one workgroup's gradient record (see k_mlp_train), and the most
+// workgroups of a training pass (one per CU).
 constexpr int kMlpRecord = 4096 + 64 + 4096 + 64 + 1024 + 16 + 1;
+constexpr int kMlpRecs = 256;
 
-hipError_t launch_mlp_forward(const MlpDev &w, const uint16_t *Xb, long long n, float *Y,
-                              hipStream_t s);
-hipError_t launch_mlp_train(const MlpDev &w, const uint16_t *Xb, const float *T, long long n,
-                            int nrec, float *partial, hipStream_t s);
-hipError_t launch_mlp_reduce(const float *partial, int nrec, int nin, int nout, float *grad,
+// X: raw FP32 rows [n][nin], standardised with mean and stdv in the kernels.
+// launch_mlp_train writes mlp_records(n) records to partial; launch_mlp_reduce
+// sums them into grad [nparams + 1]; launch_mlp_update also takes Adam step t.
+hipError_t launch_mlp_forward(const MlpDev &w, const float *mean, const float *stdv,
+                              const float *X, long long n, float *Y, hipStream_t s);
+int mlp_records(long long n);
+hipError_t launch_mlp_train(const MlpDev &w, const float *mean, const float *stdv, const float *X,
+                            const float *T, long long n, float *partial, hipStream_t s);
+hipError_t launch_mlp_reduce(const float *partial, long long n, const MlpDev &w, float *grad,
                              hipStream_t s);
-hipError_t launch_mlp_adam(float *theta, float *m, float *v, const float *grad, int np, float lr,
-                           int t, hipStream_t s);
+hipError_t launch_mlp_update(const float *partial, long long n, const MlpDev &w, float *grad,
+                             float *theta, float *m, float *v, float lr, int t, hipStream_t s);
 hipError_t launch_mlp_pack(const float *theta, int nin, int nout, const MlpDev &w,
                            hipStream_t s);
-hipError_t launch_mlp_prep(const float *X, long long n, int nin, const float *mean,
-                           const float *stdv, uint16_t *Xb, hipStream_t s);
 hipError_t launch_features(const double *obs, int nx, int ny, const float *mean,
                            const float *stdv, float *X, uint16_t *Xb, hipStream_t s);
 hipError_t launch_targets(const double *ref, const double *obs, long long N, float *T,

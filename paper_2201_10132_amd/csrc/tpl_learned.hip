@@ -51,23 +51,29 @@ __device__ __forceinline__ v4f mfma(const v4s &a, const v4s &b, const v4f &c) {
 constexpr float kInvSqrt2 = 0.70710678118654752f;
 constexpr float kInvSqrt2Pi = 0.39894228040143268f;
 
-// exact GELU z Phi(z) and its derivative Phi(z) + z phi(z)
+// exact GELU z Phi(z)
 __device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * kInvSqrt2)); }
-__device__ __forceinline__ float gelu_grad(float z) {
-  return 0.5f * (1.0f + erff(z * kInvSqrt2)) + z * kInvSqrt2Pi * expf(-0.5f * z * z);
+// and with it its derivative Phi(z) + z phi(z), from the same erf
+__device__ __forceinline__ float gelu_grad(float z, float &grad) {
+  const float e = 1.0f + erff(z * kInvSqrt2);
+  grad = 0.5f * e + z * kInvSqrt2Pi * expf(-0.5f * z * z);
+  return 0.5f * z * e;
 }
 
 // Forward pass of one 16-node tile (nodes n0 .. n0 + 15, lane column c).
-// Outputs z3 (standardised outputs 4 g + i); keeps pre-activations z1, z2
-// and the BF16 operands x, h1, h2 for the backward pass.
+// Outputs z3 (standardised outputs 4 g + i); keeps the GELU's derivatives d1,
+// d2 at the pre-activations and the BF16 operands x, h1, h2 for the backward
+// pass.
 struct Tile {
   v4s x[4];    // input, B operand per K-block
-  v4f z1[4], z2[4];
+  v4f d1[4], d2[4];
   v4s h1[4], h2[4];
   v4f z3;
 };
 
-// The three layers from the input operands already in t.x.
+// The three layers from the input operands already in t.x (GRAD: with the
+// derivatives).
+template <bool GRAD>
 __device__ __forceinline__ void tile_layers(const MlpDev &w, int c, int g, Tile &t) {
 #pragma unroll
   for (int mb = 0; mb < 4; ++mb) {
@@ -77,10 +83,13 @@ __device__ __forceinline__ void tile_layers(const MlpDev &w, int c, int g, Tile 
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb)
       acc = mfma(ld4(w.W1b + (16 * mb + c) * 64 + 16 * kb + 4 * g), t.x[kb], acc);
-    t.z1[mb] = acc;
     v4f h;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) h[i] = gelu(acc[i]);
+    for (int i = 0; i < 4; ++i) {
+      float d = 0.0f;
+      h[i] = GRAD ? gelu_grad(acc[i], d) : gelu(acc[i]);
+      t.d1[mb][i] = d;
+    }
     t.h1[mb] = pack4(h);
   }
 #pragma unroll
@@ -91,10 +100,13 @@ __device__ __forceinline__ void tile_layers(const MlpDev &w, int c, int g, Tile 
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb)
       acc = mfma(ld4(w.W2b + (16 * mb + c) * 64 + 16 * kb + 4 * g), t.h1[kb], acc);
-    t.z2[mb] = acc;
     v4f h;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) h[i] = gelu(acc[i]);
+    for (int i = 0; i < 4; ++i) {
+      float d = 0.0f;
+      h[i] = GRAD ? gelu_grad(acc[i], d) : gelu(acc[i]);
+      t.d2[mb][i] = d;
+    }
     t.h2[mb] = pack4(h);
   }
   v4f acc;
@@ -105,27 +117,56 @@ __device__ __forceinline__ void tile_layers(const MlpDev &w, int c, int g, Tile 
   t.z3 = acc;
 }
 
-__device__ __forceinline__ void tile_forward(const MlpDev &w, const uint16_t *__restrict__ Xb,
-                                             long long n, long long n0, int c, int g, Tile &t) {
-  const long long node = n0 + c;
-  const bool valid = node < n;
+// Standardisation of the inputs a lane feeds: inputs 16 kb + 4 g + i.
+struct InNorm {
+  float mean[4][4], stdv[4][4];
+};
+__device__ __forceinline__ void load_norm(const float *__restrict__ mean,
+                                          const float *__restrict__ stdv, int nin, int g,
+                                          InNorm &w) {
 #pragma unroll
   for (int kb = 0; kb < 4; ++kb)
-    t.x[kb] = valid ? ld4(Xb + node * 64 + 16 * kb + 4 * g) : v4s{0, 0, 0, 0};
-  tile_layers(w, c, g, t);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int k = 16 * kb + 4 * g + i;
+      w.mean[kb][i] = k < nin ? mean[k] : 0.0f;
+      w.stdv[kb][i] = k < nin ? stdv[k] : 1.0f;
+    }
+}
+
+// The input operands of a tile straight from the raw FP32 rows X [n][nin]:
+// standardised, rounded to BF16, zero beyond the inputs and the nodes.
+__device__ __forceinline__ void tile_inputs(const InNorm &w, const float *__restrict__ X,
+                                            long long n, int nin, long long node, int g, Tile &t) {
+  const bool valid = node < n;
+  const float *row = X + node * nin;
+#pragma unroll
+  for (int kb = 0; kb < 4; ++kb) {
+    v4s v = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int k = 16 * kb + 4 * g + i;
+      if (valid && k < nin) v[i] = bf16_bits((row[k] - w.mean[kb][i]) / w.stdv[kb][i]);
+    }
+    t.x[kb] = v;
+  }
 }
 
 }  // namespace
 
 // Y[n][nout] = network(standardised X) mapped back to physical units.
-__global__ void __launch_bounds__(256) k_mlp_forward(MlpDev w, const uint16_t *__restrict__ Xb,
-                                                     long long n, float *__restrict__ Y) {
+__global__ void __launch_bounds__(256)
+    k_mlp_forward(MlpDev w, const float *__restrict__ mean, const float *__restrict__ stdv,
+                  const float *__restrict__ X, long long n, float *__restrict__ Y) {
   const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
   const long long n0 = ((long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 16;
   if (n0 >= n) return;  // whole wave
-  Tile t;
-  tile_forward(w, Xb, n, n0, c, g, t);
   const long long node = n0 + c;
+  InNorm nm;
+  load_norm(mean, stdv, w.nin, g, nm);
+  Tile t;
+  tile_inputs(nm, X, n, w.nin, node, g, t);
+  tile_layers<false>(w, c, g, t);
   if (node < n)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -134,35 +175,52 @@ __global__ void __launch_bounds__(256) k_mlp_forward(MlpDev w, const uint16_t *_
     }
 }
 
-// Training pass: every wave walks 16-node tiles with a fixed stride, runs
-// forward and backward and accumulates the weight gradients of
-// loss = mean over nodes and outputs of (y - t)^2 (standardised targets) in
-// its registers; at the end it writes them to its record in partial[]:
+// Training pass: a workgroup of eight waves walks chunks of 128 nodes, one
+// 16-node tile per wave.  Each wave runs forward and backward on its tile and
+// stages the operands of the weight gradients transposed (units x the chunk's
+// 128 nodes, BF16) in the workgroup's LDS; the 36 16 x 16 blocks of dW1, dW2
+// and dW3 are then shared out over the waves, each contracted over all 128
+// nodes and accumulated in its wave's registers.  Gradients of
+// loss = mean over nodes and outputs of (y - t)^2 (standardised targets); at
+// the end the workgroup writes its record to partial[]:
 //   dW1 [64][64] | db1 [64] | dW2 [64][64] | db2 [64] | dW3 [16][64] |
 //   db3 [16] | sum of squared errors [1]         (kMlpRecord floats)
-// Weight gradients contract over the tile's nodes: the tile's operands are
-// staged transposed (units x 16 nodes, BF16) in the wave's LDS.
-__global__ void __launch_bounds__(64) k_mlp_train(MlpDev w, const uint16_t *__restrict__ Xb,
-                                                  const float *__restrict__ T, long long n,
-                                                  float scale, float *__restrict__ partial) {
-  __shared__ uint16_t XT[64][16], H1T[64][16], H2T[64][16], D1T[64][16], D2T[64][16],
-      DYT[16][16];
-  const int lane = threadIdx.x, c = lane & 15, g = lane >> 4;
-  v4f gW1[4][4], gW2[4][4], gW3[4];
+//
+// What bounds it: the vector ALUs (32 erf and 32 exp per lane and tile against
+// 92 matrix instructions), so every SIMD should have two waves; a wave that
+// holds all 36 blocks (144 accumulators) and walks tiles alone leaves one wave
+// on every second SIMD.  65536 rows: 108 us that way, with a launch before it
+// that wrote the standardised inputs (10 us), against 55 here.
+constexpr int kTrainWaves = 8, kTrainNodes = 16 * kTrainWaves;
+constexpr int kTrainStride = kTrainNodes + 8;  // LDS rows: 16 units of a read fall in 16 bank groups
+__global__ void __launch_bounds__(64 * kTrainWaves)
+    k_mlp_train(MlpDev w, const float *__restrict__ mean, const float *__restrict__ stdv,
+                const float *__restrict__ X, const float *__restrict__ T, long long n, float scale,
+                float *__restrict__ partial) {
+  // rows: X 0, H1 64, H2 128, dZ1 192, dZ2 256, dY 320
+  __shared__ __align__(16) uint16_t st[336][kTrainStride];
+  __shared__ float red[kTrainWaves][64 + 64 + 16 + 1];
+  const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // weight-gradient blocks wave, wave + 8, ...: 0-15 dW1, 16-31 dW2, 32-35 dW3
+  constexpr int NB = (36 + kTrainWaves - 1) / kTrainWaves;
+  v4f gW[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) gW[j] = v4f{0, 0, 0, 0};
   v4f gb1[4], gb2[4], gb3 = {0, 0, 0, 0};
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    gb1[a] = gb2[a] = gW3[a] = v4f{0, 0, 0, 0};
-#pragma unroll
-    for (int b = 0; b < 4; ++b) gW1[a][b] = gW2[a][b] = v4f{0, 0, 0, 0};
-  }
+  for (int a = 0; a < 4; ++a) gb1[a] = gb2[a] = v4f{0, 0, 0, 0};
   float sse = 0.0f;
-  const long long ntiles = (n + 15) / 16;
-  for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const long long n0 = tile * 16, node = n0 + c;
+  InNorm nm;
+  load_norm(mean, stdv, w.nin, g, nm);
+  const long long nchunks = (n + kTrainNodes - 1) / kTrainNodes;
+  for (long long chunk = blockIdx.x; chunk < nchunks; chunk += gridDim.x) {
+    const int col = 16 * wave + c;  // the node's column of the staging rows
+    const long long node = chunk * kTrainNodes + col;
     const bool valid = node < n;
     Tile t;
-    tile_forward(w, Xb, n, n0, c, g, t);
+    tile_inputs(nm, X, n, w.nin, node, g, t);
+    tile_layers<true>(w, c, g, t);
     // output error (zero outside the valid nodes and outputs)
     v4f dy;
 #pragma unroll
@@ -175,18 +233,29 @@ __global__ void __launch_bounds__(64) k_mlp_train(MlpDev w, const uint16_t *__re
     }
     gb3 += dy;
     const v4s dyb = pack4(dy);
+    auto stage = [&](int first, int mb, const v4s &v) {  // four units of the lane's node
+#pragma unroll
+      for (int i = 0; i < 4; ++i) st[first + 16 * mb + 4 * g + i][col] = (uint16_t)v[i];
+    };
+    stage(320, 0, dyb);
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb) {
+      stage(0, mb, t.x[mb]);
+      stage(64, mb, t.h1[mb]);
+      stage(128, mb, t.h2[mb]);
+    }
     // dH2 = W3^T dY, dZ2 = dH2 gelu'(z2)
     v4s dz2b[4];
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) {
       v4f acc = mfma(ld4(w.W3Tb + (16 * mb + c) * 16 + 4 * g), dyb, v4f{0, 0, 0, 0});
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] *= gelu_grad(t.z2[mb][i]);
+      for (int i = 0; i < 4; ++i) acc[i] *= t.d2[mb][i];
       dz2b[mb] = pack4(acc);
       gb2[mb] += acc;
+      stage(256, mb, dz2b[mb]);
     }
     // dH1 = W2^T dZ2, dZ1 = dH1 gelu'(z1)
-    v4s dz1b[4];
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) {
       v4f acc = {0, 0, 0, 0};
@@ -194,44 +263,26 @@ __global__ void __launch_bounds__(64) k_mlp_train(MlpDev w, const uint16_t *__re
       for (int kb = 0; kb < 4; ++kb)
         acc = mfma(ld4(w.W2Tb + (16 * mb + c) * 64 + 16 * kb + 4 * g), dz2b[kb], acc);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] *= gelu_grad(t.z1[mb][i]);
-      dz1b[mb] = pack4(acc);
+      for (int i = 0; i < 4; ++i) acc[i] *= t.d1[mb][i];
       gb1[mb] += acc;
+      stage(192, mb, pack4(acc));
     }
-    // stage the operands transposed: unit rows, node columns
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int u = 16 * mb + 4 * g + i;
-        XT[u][c] = (uint16_t)t.x[mb][i];
-        H1T[u][c] = (uint16_t)t.h1[mb][i];
-        H2T[u][c] = (uint16_t)t.h2[mb][i];
-        D1T[u][c] = (uint16_t)dz1b[mb][i];
-        D2T[u][c] = (uint16_t)dz2b[mb][i];
-      }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) DYT[4 * g + i][c] = (uint16_t)dyb[i];
     __syncthreads();
-    // dW1 += dZ1^T X, dW2 += dZ2^T H1, dW3 += dY^T H2 (K = the 16 nodes)
+    // dW1 += dZ1^T X, dW2 += dZ2^T H1, dW3 += dY^T H2 (K = the chunk's nodes)
 #pragma unroll
-    for (int mo = 0; mo < 4; ++mo) {
-      const v4s a1 = ld4(&D1T[16 * mo + c][4 * g]);
-      const v4s a2 = ld4(&D2T[16 * mo + c][4 * g]);
+    for (int j = 0; j < NB; ++j) {
+      const int b = wave + kTrainWaves * j;  // wave-uniform
+      if (b < 36) {
+        const int ra = b < 16 ? 192 + 16 * (b >> 2) : b < 32 ? 256 + 16 * ((b - 16) >> 2) : 320;
+        const int rb = b < 16 ? 16 * (b & 3) : b < 32 ? 64 + 16 * (b & 3) : 128 + 16 * (b & 3);
 #pragma unroll
-      for (int mi = 0; mi < 4; ++mi) {
-        gW1[mo][mi] = mfma(a1, ld4(&XT[16 * mi + c][4 * g]), gW1[mo][mi]);
-        gW2[mo][mi] = mfma(a2, ld4(&H1T[16 * mi + c][4 * g]), gW2[mo][mi]);
+        for (int kb = 0; kb < kTrainNodes / 16; ++kb)
+          gW[j] = mfma(ld4(&st[ra + c][16 * kb + 4 * g]), ld4(&st[rb + c][16 * kb + 4 * g]), gW[j]);
       }
     }
-    {
-      const v4s a3 = ld4(&DYT[c][4 * g]);
-#pragma unroll
-      for (int mi = 0; mi < 4; ++mi) gW3[mi] = mfma(a3, ld4(&H2T[16 * mi + c][4 * g]), gW3[mi]);
-    }
-    __syncthreads();  // the next tile overwrites the staging arrays
+    __syncthreads();  // the next chunk overwrites the staging rows
   }
-  // bias gradients: sum over the 16 node columns of each lane group
+  // bias gradients: sum over the 16 node columns of each lane group, then the waves
 #pragma unroll
   for (int m = 1; m < 16; m <<= 1) {
 #pragma unroll
@@ -246,81 +297,123 @@ __global__ void __launch_bounds__(64) k_mlp_train(MlpDev w, const uint16_t *__re
   }
 #pragma unroll
   for (int m = 1; m < 64; m <<= 1) sse += __shfl_xor(sse, m);
+  if (c == 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+      for (int mb = 0; mb < 4; ++mb) {
+        red[wave][16 * mb + 4 * g + i] = gb1[mb][i];
+        red[wave][64 + 16 * mb + 4 * g + i] = gb2[mb][i];
+      }
+      red[wave][128 + 4 * g + i] = gb3[i];
+    }
+    if (g == 0) red[wave][144] = sse;
+  }
+  __syncthreads();
   float *rec = partial + (size_t)blockIdx.x * kMlpRecord;
   float *pW1 = rec, *pb1 = pW1 + 4096, *pW2 = pb1 + 64, *pb2 = pW2 + 4096, *pW3 = pb2 + 64,
         *pb3 = pW3 + 1024, *psse = pb3 + 16;
 #pragma unroll
-  for (int mo = 0; mo < 4; ++mo)
+  for (int j = 0; j < NB; ++j) {
+    const int b = wave + kTrainWaves * j;
+    if (b < 36) {
+      float *dst = b < 16 ? pW1 : b < 32 ? pW2 : pW3;
+      const int mo = b < 32 ? (b & 15) >> 2 : 0, mi = b & 3;
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        pW1[(16 * mo + 4 * g + i) * 64 + 16 * mi + c] = gW1[mo][mi][i];
-        pW2[(16 * mo + 4 * g + i) * 64 + 16 * mi + c] = gW2[mo][mi][i];
-      }
-#pragma unroll
-  for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) pW3[(4 * g + i) * 64 + 16 * mi + c] = gW3[mi][i];
-  if (c == 0) {
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        pb1[16 * mb + 4 * g + i] = gb1[mb][i];
-        pb2[16 * mb + 4 * g + i] = gb2[mb][i];
-      }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) pb3[4 * g + i] = gb3[i];
+      for (int i = 0; i < 4; ++i) dst[(16 * mo + 4 * g + i) * 64 + 16 * mi + c] = gW[j][i];
+    }
   }
-  if (lane == 0) psse[0] = sse;
+  if (threadIdx.x < 145) {
+    const int j = threadIdx.x;
+    double s = 0.0;
+    for (int v = 0; v < kTrainWaves; ++v) s += red[v][j];
+    float *dst = j < 64 ? pb1 + j : j < 128 ? pb2 + j - 64 : j < 144 ? pb3 + j - 128 : psse;
+    *dst = (float)s;
+  }
 }
 
-// Sum the per-wave records in FP64 (fixed order) and scatter them to the
-// canonical parameter layout W1 [64][nin] b1 W2 [64][64] b2 W3 [nout][64] b3;
-// out[nparams] receives the sum of squared errors.
-__global__ void k_mlp_reduce(const float *__restrict__ partial, int nrec, int nin, int nout,
-                             float *__restrict__ grad) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= kMlpRecord) return;
-  double s = 0.0;
-  for (int r = 0; r < nrec; ++r) s += partial[(size_t)r * kMlpRecord + j];
-  // record position -> canonical position (or -1 for padding)
-  int dst = -1;
-  const int oW1 = 0, ob1 = 64 * nin, oW2 = ob1 + 64, ob2 = oW2 + 4096, oW3 = ob2 + 64,
+// Record position -> canonical position (parameters, then the sum of squared
+// errors at nparams), or -1 for padding.
+__device__ __forceinline__ int canonical(int j, int nin, int nout) {
+  const int ob1 = 64 * nin, oW2 = ob1 + 64, ob2 = oW2 + 4096, oW3 = ob2 + 64,
             ob3 = oW3 + 64 * nout, osse = ob3 + nout;
-  if (j < 4096) {
-    const int h = j / 64, i = j % 64;
-    if (i < nin) dst = oW1 + h * nin + i;
-  } else if (j < 4160) {
-    dst = ob1 + (j - 4096);
-  } else if (j < 8256) {
-    dst = oW2 + (j - 4160);
-  } else if (j < 8320) {
-    dst = ob2 + (j - 8256);
-  } else if (j < 9344) {
-    const int o = (j - 8320) / 64, h = (j - 8320) % 64;
-    if (o < nout) dst = oW3 + o * 64 + h;
-  } else if (j < 9360) {
-    if (j - 9344 < nout) dst = ob3 + (j - 9344);
-  } else {
-    dst = osse;
-  }
-  if (dst >= 0) grad[dst] = (float)s;
+  if (j < 4096) return j % 64 < nin ? (j / 64) * nin + j % 64 : -1;
+  if (j < 4160) return ob1 + (j - 4096);
+  if (j < 8256) return oW2 + (j - 4160);
+  if (j < 8320) return ob2 + (j - 8256);
+  if (j < 9344) return (j - 8320) / 64 < nout ? oW3 + (j - 8320) : -1;
+  if (j < 9360) return j - 9344 < nout ? ob3 + (j - 9344) : -1;
+  return osse;
 }
 
-// Adam (Kingma & Ba 2015) on the FP32 master parameters; t >= 1.
-__global__ void k_mlp_adam(float *__restrict__ theta, float *__restrict__ m,
-                           float *__restrict__ v, const float *__restrict__ grad, int np,
-                           float lr, float b1, float b2, float eps, float c1, float c2) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= np) return;
-  const float gj = grad[j];
-  const float mj = b1 * m[j] + (1.0f - b1) * gj;
-  const float vj = b2 * v[j] + (1.0f - b2) * gj * gj;
-  m[j] = mj;
-  v[j] = vj;
-  theta[j] -= lr * (mj / c1) / (sqrtf(vj / c2) + eps);
+// A parameter's copies in the operand arrays (BF16 weights, zero padded by
+// k_mlp_pack, W2 and W3 also transposed; padded FP32 biases); j is its record
+// position.
+__device__ __forceinline__ void put_operand(int j, float v, const MlpDev &w) {
+  uint16_t *W1b = const_cast<uint16_t *>(w.W1b), *W2b = const_cast<uint16_t *>(w.W2b),
+           *W3b = const_cast<uint16_t *>(w.W3b), *W2Tb = const_cast<uint16_t *>(w.W2Tb),
+           *W3Tb = const_cast<uint16_t *>(w.W3Tb);
+  const uint16_t h = (uint16_t)bf16_bits(v);
+  if (j < 4096) {
+    W1b[j] = h;
+  } else if (j < 4160) {
+    const_cast<float *>(w.b1)[j - 4096] = v;
+  } else if (j < 8256) {
+    const int i = j - 4160;
+    W2b[i] = h;
+    W2Tb[(i % 64) * 64 + i / 64] = h;
+  } else if (j < 8320) {
+    const_cast<float *>(w.b2)[j - 8256] = v;
+  } else if (j < 9344) {
+    const int i = j - 8320;
+    W3b[i] = h;
+    W3Tb[(i % 64) * 16 + i / 64] = h;
+  } else {
+    const_cast<float *>(w.b3)[j - 9344] = v;
+  }
+}
+
+// Adam's constants of one step (Kingma & Ba 2015); bias corrections c1, c2.
+struct AdamStep {
+  float *theta, *m, *v;
+  float lr, b1, b2, eps, c1, c2;
+};
+
+// Sum the workgroups' records in FP64 (fixed order) into grad (canonical
+// layout, then the sum of squared errors); with ADAM also take the step on
+// the FP32 master parameters and renew their operand copies.  32 record
+// positions per workgroup, eight threads each: a thread that walks all the
+// records of its position alone takes 126 us for 512 of them on 37
+// workgroups, and Adam and the packing were two more launches (11 us); here 6.
+template <bool ADAM>
+__global__ void __launch_bounds__(256)
+    k_mlp_reduce(const float *__restrict__ partial, int nrec, MlpDev w, float *__restrict__ grad,
+                 AdamStep ad) {
+  __shared__ double part[8][32];
+  const int jj = threadIdx.x & 31, sl = threadIdx.x >> 5;
+  const int j = blockIdx.x * 32 + jj;
+  double s = 0.0;
+  if (j < kMlpRecord) {
+#pragma unroll 8
+    for (int r = sl; r < nrec; r += 8) s += partial[(size_t)r * kMlpRecord + j];
+  }
+  part[sl][jj] = s;
+  __syncthreads();
+  if (sl != 0 || j >= kMlpRecord) return;
+  for (int i = 1; i < 8; ++i) s += part[i][jj];
+  const int dst = canonical(j, w.nin, w.nout);
+  if (dst < 0) return;
+  const float gj = (float)s;
+  grad[dst] = gj;
+  if (ADAM && j < kMlpRecord - 1) {
+    const float mj = ad.b1 * ad.m[dst] + (1.0f - ad.b1) * gj;
+    const float vj = ad.b2 * ad.v[dst] + (1.0f - ad.b2) * gj * gj;
+    ad.m[dst] = mj;
+    ad.v[dst] = vj;
+    const float th = ad.theta[dst] - ad.lr * (mj / ad.c1) / (sqrtf(vj / ad.c2) + ad.eps);
+    ad.theta[dst] = th;
+    put_operand(j, th, w);
+  }
 }
 
 // Canonical FP32 parameters -> BF16 operand arrays (zero padded) and
@@ -351,17 +444,6 @@ __global__ void k_mlp_pack(const float *__restrict__ theta, int nin, int nout,
     b2[j] = B2[j];
   }
   if (j < 16) b3[j] = j < nout ? B3[j] : 0.0f;
-}
-
-// Raw FP32 inputs [n][nin] -> standardised BF16 operand rows [n][64].
-__global__ void k_mlp_prep(const float *__restrict__ X, long long n, int nin,
-                           const float *__restrict__ mean, const float *__restrict__ stdv,
-                           uint16_t *__restrict__ Xb) {
-  const long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n * 64) return;
-  const long long node = j / 64;
-  const int k = (int)(j % 64);
-  Xb[j] = (uint16_t)bf16_bits(k < nin ? (X[node * nin + k] - mean[k]) / stdv[k] : 0.0f);
 }
 
 // ---------------------------------------------------------------------------
@@ -614,7 +696,7 @@ __global__ void __launch_bounds__(256) k_correct(MlpDev w, const double *__restr
       }
       t.x[kb] = v;
     }
-    tile_layers(w, c, g, t);
+    tile_layers<false>(w, c, g, t);
     if (valid)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -681,35 +763,42 @@ __global__ void __launch_bounds__(256) k_source_gate(const float *__restrict__ c
 // ---------------------------------------------------------------------------
 // Launchers
 
-hipError_t launch_mlp_forward(const MlpDev &w, const uint16_t *Xb, long long n, float *Y,
-                              hipStream_t s) {
+hipError_t launch_mlp_forward(const MlpDev &w, const float *mean, const float *stdv,
+                              const float *X, long long n, float *Y, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const long long tiles = (n + 15) / 16;
-  hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, s, w, Xb,
-                     n, Y);
+  hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, s, w, mean,
+                     stdv, X, n, Y);
   return hipGetLastError();
 }
 
-hipError_t launch_mlp_train(const MlpDev &w, const uint16_t *Xb, const float *T, long long n,
-                            int nrec, float *partial, hipStream_t s) {
+int mlp_records(long long n) {
+  const long long chunks = (n + kTrainNodes - 1) / kTrainNodes;
+  return (int)std::min<long long>(chunks, kMlpRecs);
+}
+
+hipError_t launch_mlp_train(const MlpDev &w, const float *mean, const float *stdv, const float *X,
+                            const float *T, long long n, float *partial, hipStream_t s) {
   const float scale = 2.0f / (float)((double)n * w.nout);
-  hipLaunchKernelGGL(k_mlp_train, dim3(nrec), dim3(64), 0, s, w, Xb, T, n, scale, partial);
+  hipLaunchKernelGGL(k_mlp_train, dim3(mlp_records(n)), dim3(64 * kTrainWaves), 0, s, w, mean,
+                     stdv, X, T, n, scale, partial);
   return hipGetLastError();
 }
 
-hipError_t launch_mlp_reduce(const float *partial, int nrec, int nin, int nout, float *grad,
+hipError_t launch_mlp_reduce(const float *partial, long long n, const MlpDev &w, float *grad,
                              hipStream_t s) {
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((kMlpRecord + 255) / 256), dim3(256), 0, s, partial,
-                     nrec, nin, nout, grad);
+  hipLaunchKernelGGL(k_mlp_reduce<false>, dim3((kMlpRecord + 31) / 32), dim3(256), 0, s, partial,
+                     mlp_records(n), w, grad, AdamStep{});
   return hipGetLastError();
 }
 
-hipError_t launch_mlp_adam(float *theta, float *m, float *v, const float *grad, int np, float lr,
-                           int t, hipStream_t s) {
+hipError_t launch_mlp_update(const float *partial, long long n, const MlpDev &w, float *grad,
+                             float *theta, float *m, float *v, float lr, int t, hipStream_t s) {
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
   const float c1 = (float)(1.0 - std::pow(0.9, t)), c2 = (float)(1.0 - std::pow(0.999, t));
-  hipLaunchKernelGGL(k_mlp_adam, dim3((np + 255) / 256), dim3(256), 0, s, theta, m, v, grad, np,
-                     lr, b1, b2, eps, c1, c2);
+  const AdamStep ad{theta, m, v, lr, b1, b2, eps, c1, c2};
+  hipLaunchKernelGGL(k_mlp_reduce<true>, dim3((kMlpRecord + 31) / 32), dim3(256), 0, s, partial,
+                     mlp_records(n), w, grad, ad);
   return hipGetLastError();
 }
 
@@ -720,14 +809,6 @@ hipError_t launch_mlp_pack(const float *theta, int nin, int nout, const MlpDev &
                      const_cast<uint16_t *>(w.W3b), const_cast<uint16_t *>(w.W2Tb),
                      const_cast<uint16_t *>(w.W3Tb), const_cast<float *>(w.b1),
                      const_cast<float *>(w.b2), const_cast<float *>(w.b3));
-  return hipGetLastError();
-}
-
-hipError_t launch_mlp_prep(const float *X, long long n, int nin, const float *mean,
-                           const float *stdv, uint16_t *Xb, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_mlp_prep, dim3((unsigned)((n * 64 + 255) / 256)), dim3(256), 0, s, X, n,
-                     nin, mean, stdv, Xb);
   return hipGetLastError();
 }
 

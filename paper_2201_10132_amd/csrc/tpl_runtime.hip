@@ -2523,15 +2523,10 @@ struct tpl_mlp {
   uint16_t *wb = nullptr;              // W1b | W2b | W3b | W2Tb | W3Tb
   float *fb = nullptr;                 // b1[64] b2[64] b3[16] | norm (160)
   float *partial = nullptr;
-  int nrec = 0;
-  uint16_t *xb = nullptr;
-  long long xb_n = 0;
   int t = 0;  // Adam steps taken
 };
 
 namespace {
-
-constexpr int kMlpRecs = 512;  // gradient records (waves) of a training pass
 
 MlpDev mlp_dev(const tpl_mlp *m) {
   MlpDev w;
@@ -2570,7 +2565,6 @@ int mlp_ready(tpl_mlp *m) {
       !alloc((void **)&m->wb, 14336 * 2) || !alloc((void **)&m->fb, (144 + 160) * 4) ||
       !alloc((void **)&m->partial, (size_t)kMlpRecs * kMlpRecord * 4))
     return fail(TPL_ENOMEM, "network allocation failed");
-  m->nrec = kMlpRecs;
   HIPCHK(hipMemcpyAsync(m->theta, m->theta_h.data(), np * 4, hipMemcpyHostToDevice, m->stream));
   HIPCHK(hipMemsetAsync(m->m, 0, np * 4, m->stream));
   HIPCHK(hipMemsetAsync(m->v, 0, np * 4, m->stream));
@@ -2582,29 +2576,12 @@ int mlp_ready(tpl_mlp *m) {
   return TPL_OK;
 }
 
-int mlp_inputs(tpl_mlp *m, const float *X, long long n) {
-  if (n > m->xb_n) {
-    if (m->xb) HIPCHK(hipFree(m->xb));
-    m->xb = nullptr;
-    m->xb_n = 0;
-    if (hipMalloc(&m->xb, (size_t)n * 64 * 2) != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(TPL_ENOMEM, "input staging allocation failed");
-    }
-    m->xb_n = n;
-  }
-  HIPCHK(launch_mlp_prep(X, n, m->nin, mlp_in_mean(m), mlp_in_std(m), m->xb, m->stream));
-  return TPL_OK;
-}
-
-// One training pass: gradients (canonical layout) and sum of squared errors
-// in m->grad[np].
+// One training pass: per-workgroup gradient records in m->partial.
 int mlp_pass(tpl_mlp *m, const float *X, const float *T, long long n) {
-  int rc = mlp_ready(m);
-  if (!rc) rc = mlp_inputs(m, X, n);
+  const int rc = mlp_ready(m);
   if (rc) return rc;
-  HIPCHK(launch_mlp_train(mlp_dev(m), m->xb, T, n, m->nrec, m->partial, m->stream));
-  HIPCHK(launch_mlp_reduce(m->partial, m->nrec, m->nin, m->nout, m->grad, m->stream));
+  HIPCHK(launch_mlp_train(mlp_dev(m), mlp_in_mean(m), mlp_in_std(m), X, T, n, m->partial,
+                          m->stream));
   return TPL_OK;
 }
 
@@ -2773,10 +2750,9 @@ int tpl_mlp_forward(tpl_mlp *m, const float *X, float *Y, int64_t n) {
   if (!m || (n > 0 && (!X || !Y))) return fail(TPL_EINVAL, "null argument");
   if (n < 0) return fail(TPL_EINVAL, "n must be >= 0");
   if (n == 0) return TPL_OK;
-  int rc = mlp_ready(m);
-  if (!rc) rc = mlp_inputs(m, X, n);
+  const int rc = mlp_ready(m);
   if (rc) return rc;
-  HIPCHK(launch_mlp_forward(mlp_dev(m), m->xb, n, Y, m->stream));
+  HIPCHK(launch_mlp_forward(mlp_dev(m), mlp_in_mean(m), mlp_in_std(m), X, n, Y, m->stream));
   HIPCHK(hipStreamSynchronize(m->stream));
   return TPL_OK;
 }
@@ -2787,6 +2763,7 @@ int tpl_mlp_grads(tpl_mlp *m, const float *X, const float *T, int64_t n, float *
   if (n < 1) return fail(TPL_EINVAL, "n must be >= 1");
   int rc = mlp_pass(m, X, T, n);
   if (rc) return rc;
+  HIPCHK(launch_mlp_reduce(m->partial, n, mlp_dev(m), m->grad, m->stream));
   std::vector<float> g(m->np + 1);
   HIPCHK(hipMemcpyAsync(g.data(), m->grad, (m->np + 1) * 4, hipMemcpyDeviceToHost, m->stream));
   HIPCHK(hipStreamSynchronize(m->stream));
@@ -2803,8 +2780,8 @@ int tpl_mlp_train_step(tpl_mlp *m, const float *X, const float *T, int64_t n, fl
   int rc = mlp_pass(m, X, T, n);
   if (rc) return rc;
   m->t += 1;
-  HIPCHK(launch_mlp_adam(m->theta, m->m, m->v, m->grad, m->np, lr, m->t, m->stream));
-  HIPCHK(launch_mlp_pack(m->theta, m->nin, m->nout, mlp_dev(m), m->stream));
+  HIPCHK(launch_mlp_update(m->partial, n, mlp_dev(m), m->grad, m->theta, m->m, m->v, lr, m->t,
+                           m->stream));
   if (loss) {
     float sse = 0.0f;
     HIPCHK(hipMemcpyAsync(&sse, m->grad + m->np, 4, hipMemcpyDeviceToHost, m->stream));
@@ -2824,7 +2801,6 @@ void tpl_mlp_destroy(tpl_mlp *m) {
   (void)hipFree(m->wb);
   (void)hipFree(m->fb);
   (void)hipFree(m->partial);
-  (void)hipFree(m->xb);
   delete m;
 }
 
