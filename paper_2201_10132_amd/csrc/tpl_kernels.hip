@@ -86,8 +86,14 @@ __device__ __forceinline__ void step_tile(const StepParams &p, const StateT<T> &
     osrc[d] = SZ * (uint32_t)(sy * nx + sx);
     fsrc[d] = 8u * (uint32_t)(sy * nx + sx);
   }
-  auto plane = [&](const T *arr, long long i) { return uni(arr + (size_t)i * N); };
-  auto wplane = [&](T *arr, long long i) { return uni(arr + (size_t)i * N); };
+  // plane bases: 32 x 32 bit products (a plane is below 2^32 bytes)
+  const uint32_t NT = SZ * (uint32_t)N;
+  auto plane = [&](const T *arr, uint32_t i) {
+    return uni(reinterpret_cast<const T *>(reinterpret_cast<const char *>(arr) + (uint64_t)i * NT));
+  };
+  auto wplane = [&](T *arr, uint32_t i) {
+    return uni(reinterpret_cast<T *>(reinterpret_cast<char *>(arr) + (uint64_t)i * NT));
+  };
   auto fplane = [&](const double *arr, long long i) { return uni(arr + (size_t)i * N); };
   auto wfplane = [&](double *arr, long long i) { return uni(arr + (size_t)i * N); };
   // FP32 form: reference values, [row][q][k] / [row][q] / [row][d]
@@ -164,6 +170,9 @@ __device__ __forceinline__ void step_tile(const StepParams &p, const StateT<T> &
   for (int d = 0; d < 9; ++d) mg[d] = 0.0;
   double Mxx = 0.0, Mxy = 0.0, Myy = 0.0;
   const int nqd = p.nqd;
+  uint32_t hsrc[9];  // BF16 form: the pull sources' byte offsets in a 16-bit plane
+#pragma unroll
+  for (int d = 0; d < 9; ++d) hsrc[d] = osrc[d] >> 1;
   const bool qsync = (p.wg >> 16) & 1;  // only with qs == 1: equal trip counts
   for (int q = slice; q < nqd; q += p.qs) {
     if (qsync) __syncthreads();  // keep the group's waves on the same Q-node
@@ -174,6 +183,7 @@ __device__ __forceinline__ void step_tile(const StepParams &p, const StateT<T> &
     using GT = std::conditional_t<B16, float, double>;
     GT g[25];
     float rest_res = 0.0f;  // BF16 form: rounding residual of velocities 1..24
+    uint32_t hout[12];      // and their rounded deviations, two by two
     auto G = [&](int k) -> double {
       if constexpr (B16) return rq(rpull, y, q, k) + (double)g[k];
       else return g[k];
@@ -198,12 +208,22 @@ __device__ __forceinline__ void step_tile(const StepParams &p, const StateT<T> &
       // BF16 form: the 24 pulled deviations, 16 bits each, at half the byte
       // offsets of the FP32 planes; the node's own rest population in FP32
       // from its two 16-bit halves (planes 0 and 25)
-      const uint16_t *xp = reinterpret_cast<const uint16_t *>(a.XP);
+      // The offsets are made opaque per Q-node, or their zero extensions are
+      // hoisted out of the loop and every access pays a 64-bit vector add
+      // (this form is bound by its vector instructions, 1040 per Q-node with
+      // those adds and an integer rounding, 810 without: 6.05 -> 5.5 ms per
+      // step at 1024 x 1024, NQ 16, 4.1 -> 4.5 TB/s).
+      const char *xp = reinterpret_cast<const char *>(a.XP);
+      auto hplane = [&](int i) {
+        return uni(reinterpret_cast<const uint16_t *>(xp + (uint64_t)(uint32_t)i * (NT >> 1)));
+      };
+#pragma unroll
+      for (int d = 0; d < 9; ++d) asm volatile("" : "+v"(hsrc[d]));
 #pragma unroll
       for (int k = 1; k < 25; ++k)
-        g[k] = (float)from_bf16(ldo(uni(xp + (size_t)qn.plane[k] * N), osrc[pdir(k)] >> 1));
-      const uint32_t hi = ldo(uni(xp + (size_t)q * N), oR >> 1);
-      const uint32_t lo = ldo(uni(xp + (size_t)(25 * nqd + q) * N), oR >> 1);
+        g[k] = (float)from_bf16(ldo(hplane(qn.plane[k]), hsrc[pdir(k)]));
+      const uint32_t hi = ldo(hplane(q), hsrc[0]);
+      const uint32_t lo = ldo(hplane(25 * nqd + q), hsrc[0]);
       g[0] = __uint_as_float((hi << 16) | lo);
     }
     const PolyMoments<QE2> m = polymer_moments<QE2>(G);
@@ -233,7 +253,12 @@ __device__ __forceinline__ void step_tile(const StepParams &p, const StateT<T> &
         // residual is exact in FP32)
         const float dv = (float)(go - rq(rstore, y, q, k));
         g[k] = dv;
-        if (k > 0) rest_res += dv - (float)from_bf16(to_bf16(dv));
+        if (k > 0 && k % 2 == 0) {  // velocities k - 1 and k, in this order
+          const uint32_t h = to_bf16_pair(g[k - 1], dv);
+          rest_res += g[k - 1] - __uint_as_float(h << 16);
+          rest_res += dv - __uint_as_float(h & 0xffff0000u);
+          hout[k / 2 - 1] = h;
+        }
       } else {
         g[k] = go;
       }
@@ -267,17 +292,20 @@ __device__ __forceinline__ void step_tile(const StepParams &p, const StateT<T> &
         // BF16 form: the 24 deviations (from the store reference) rounded to
         // 16 bits, the rest population's FP32 bits split over planes 0 and
         // 25; plane stride opaque as above
-        sto(wplane(b.PSI, q), oR, stored<T>(psi, rpq(y, q)));
-        uint64_t stride = (uint64_t)nqd * (uint64_t)N * 2u;
+        asm volatile("" : "+v"(hsrc[0]));  // as before the loads
+        sto(wplane(b.PSI, q), 2u * hsrc[0], stored<T>(psi, rpq(y, q)));
+        uint64_t stride = (uint64_t)(uint32_t)nqd * (NT >> 1);
         asm volatile("" : "+s"(stride));
-        char *pw = reinterpret_cast<char *>(uni(reinterpret_cast<uint16_t *>(b.XP) + (size_t)q * N));
+        char *pw = reinterpret_cast<char *>(b.XP) + (uint64_t)(uint32_t)q * (NT >> 1);
+        auto put = [&](int k, uint16_t v) {
+          sto(uni(reinterpret_cast<uint16_t *>(pw + (size_t)k * stride)), hsrc[0], v);
+        };
         const uint32_t u0 = __float_as_uint(g[0]);
-        sto(reinterpret_cast<uint16_t *>(pw), oR >> 1, (uint16_t)(u0 >> 16));
+        put(0, (uint16_t)(u0 >> 16));
 #pragma unroll
         for (int k = 1; k < 25; ++k)
-          sto(reinterpret_cast<uint16_t *>(pw + (size_t)k * stride), oR >> 1, to_bf16(g[k]));
-        sto(reinterpret_cast<uint16_t *>(pw + (size_t)25 * stride), oR >> 1,
-            (uint16_t)(u0 & 0xffffu));
+          put(k, (uint16_t)(k % 2 ? hout[k / 2] & 0xffffu : hout[k / 2 - 1] >> 16));
+        put(25, (uint16_t)(u0 & 0xffffu));
       }
     }
     Mxx = fma(psi * qn.qx, qn.fx, Mxx);
@@ -943,7 +971,7 @@ template hipError_t launch_same_step_fields<float>(const StepParams &, StateT<fl
 __device__ __forceinline__ double rest_with_residual(double rest, const double *d) {
   double e = 0.0;
 #pragma unroll
-  for (int k = 1; k < 25; ++k) e += d[k] - from_bf16(to_bf16(d[k]));
+  for (int k = 1; k < 25; ++k) e += d[k] - from_bf16(to_bf16((float)d[k]));
   return rest + e;
 }
 
@@ -965,7 +993,7 @@ __global__ void k_bf16_encode(long long nq, const float *__restrict__ dev,
 #pragma unroll
   for (int k = 0; k < 25; ++k) d[k] = dev[k * nq + j];
 #pragma unroll
-  for (int k = 1; k < 25; ++k) dst[k * nq + j] = to_bf16(d[k]);
+  for (int k = 1; k < 25; ++k) dst[k * nq + j] = to_bf16((float)d[k]);
   const uint32_t u = __float_as_uint((float)rest_with_residual(d[0], d));
   dst[j] = (uint16_t)(u >> 16);
   dst[25 * nq + j] = (uint16_t)(u & 0xffffu);

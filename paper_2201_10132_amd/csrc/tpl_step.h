@@ -140,10 +140,18 @@ __device__ __forceinline__ float stored<float>(double v, double ref) { return (f
 // even) of its deviation from the FP32 reference, the x-invariant base state;
 // solvent and psi keep FP32 deviations.  BF16 has FP32's exponent range, so
 // the deviations need no scaling.
-__device__ __forceinline__ uint16_t to_bf16(double v) {
-  uint32_t u = __float_as_uint((float)v);
-  u += 0x7fffu + ((u >> 16) & 1u);  // round to nearest even
-  return (uint16_t)(u >> 16);
+// Rounds two FP32 values in one instruction, a to the lower half.
+__device__ __forceinline__ uint32_t to_bf16_pair(float a, float b) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 h2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), h2));
+}
+// One value.  (The empty asm hides where it comes from: the compiler would
+// fuse an FP64-to-FP32 rounding before it into one rounding to BF16, another
+// value; it does not do so with pairs, where the asm costs 20 % of the step.)
+__device__ __forceinline__ uint16_t to_bf16(float v) {
+  asm("" : "+v"(v));
+  return __builtin_bit_cast(uint16_t, (__bf16)v);
 }
 __device__ __forceinline__ double from_bf16(uint16_t b) {
   return (double)__uint_as_float(((uint32_t)b) << 16);

@@ -76,3 +76,29 @@ def test_narrow_is_bitwise_the_wide_kernel(precision, option):
         assert np.array_equal(b.instance(i).moments(), t.moments()), i
         t.close()
     b.close()
+
+
+@pytest.mark.parametrize("precision", [P.TPL_FP64, P.TPL_FP32, P.TPL_BF16],
+                         ids=["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("nq,option", [(6, {}), (12, {}), (12, dict(qe_model=2, tau_ratio_p=0.5))],
+                         ids=["nq6", "nq12", "nq12model2"])
+def test_narrow_is_bitwise_the_wide_kernel_on_a_repeated_state(precision, nq, option):
+    """A state that repeats along x stays so, bit for bit: the 64 x 40 lattice
+    takes the narrow kernel, three or four of it side by side the wide one."""
+    print(f"narrow vs wide repeated {precision} nq={nq} {option}", flush=True)
+    kw = dict(periods=1, nq=nq, pre_steps=30, qsplit=8, precision=precision, autotune=0, **option)
+    rep = 3 if nq == 6 else 4
+    one = P.Tpl(64, 40, 20.0, 0.5, 0.8, **kw)
+    many = P.Tpl(64 * rep, 40, 20.0, 0.5, 0.8, **kw)
+    one.init(seed=2, perturbation=1e-2)
+    many.init(seed=0, perturbation=0.0)
+    st = one.get_state()
+    one.set_state(**st)
+    many.set_state(**{k: np.tile(v, (1,) * (v.ndim - 1) + (rep,)) for k, v in st.items()})
+    one.step(5)
+    many.step(5)
+    a, b = one.get_state(), many.get_state()
+    for k in a:
+        assert np.array_equal(np.tile(a[k], (1,) * (a[k].ndim - 1) + (rep,)), b[k]), k
+    one.close()
+    many.close()
