@@ -27,8 +27,8 @@ namespace tplk {
 // relaxation; write 25 populations and psi; accumulate the new marginals and
 // M.  The slices' partial marginals are summed in LDS in a fixed order.
 // Arithmetic is FP64 for both storage types.  ROWTILE: every 64-node tile
-// lies in one lattice row (nx % 64 == 0), so the FP32 form's reference values
-// are wave-uniform (scalar loads).
+// lies in one lattice row (the last of a row may have idle lanes), so the FP32
+// and BF16 forms' reference values are wave-uniform (scalar loads).
 // One 64-node tile of one lattice (all qs slices of the workgroup take part).
 // red: LDS of qs * 12 * 64 doubles.
 // In-place streaming (IP != 0; one population array, a == b for XS and XP;
@@ -63,13 +63,23 @@ __device__ __forceinline__ void step_tile(const StepParams &p, const StateT<T> &
   const int lane = threadIdx.x & 63;
   const int slice = p.qs > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const long long N = p.N;
-  const long long rr = (long long)tile * 64 + lane;
-  const bool active = rr < N;
-  const int r = (int)(active ? rr : N - 1);
   const int nx = p.nx, ny = p.ny;
-  int y = r / nx;
-  const int x = r - y * nx;
-  if (ROWTILE) y = __builtin_amdgcn_readfirstlane(y);
+  int x, y;
+  bool active;
+  if constexpr (ROWTILE) {
+    const int tpr = (nx + 63) >> 6;
+    y = __builtin_amdgcn_readfirstlane(tile / tpr);
+    x = (tile - y * tpr) * 64 + lane;
+    active = x < nx && y < ny;  // the last group's waves may have no tile
+    x = x < nx ? x : nx - 1;
+    y = y < ny ? y : ny - 1;
+  } else {
+    const long long rr = (long long)tile * 64 + lane;
+    active = rr < N;
+    y = (int)(active ? rr : N - 1) / nx;
+    x = (int)(active ? rr : N - 1) - y * nx;
+  }
+  const int r = y * nx + x;
   const int xm = (x == 0) ? nx - 1 : x - 1, xp = (x == nx - 1) ? 0 : x + 1;
   const int ym = (y == 0) ? ny - 1 : y - 1, yp = (y == ny - 1) ? 0 : y + 1;
   const uint32_t oR = SZ * (uint32_t)r;
@@ -361,14 +371,18 @@ __global__ void __launch_bounds__(MAXT)
     tile = xcd_tile(blockIdx.x, p.tiles_per_xcd);
     if (tile >= p.ntiles) return;  // whole workgroup leaves together
   } else {
-    // a group of gx x gy tiles (one wave each) of gy consecutive rows;
-    // tiles_per_xcd counts groups
+    // a group of gx x gy tiles (one wave each) of gy consecutive rows, or of
+    // gx consecutive tiles; tiles_per_xcd counts groups
     const int gx = p.wg & 255, gy = (p.wg >> 8) & 255;
     const int grp = xcd_tile(blockIdx.x, p.tiles_per_xcd);
     if (grp * gx * gy >= p.ntiles) return;  // whole workgroup leaves together
-    const int tpr = p.nx >> 6, gpr = tpr / gx;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    tile = ((grp / gpr) * gy + w / gx) * tpr + (grp % gpr) * gx + w % gx;
+    if (gy == 1) {
+      tile = grp * gx + w;
+    } else {
+      const int tpr = p.nx >> 6, gpr = tpr / gx;
+      tile = ((grp / gpr) * gy + w / gx) * tpr + (grp % gpr) * gx + w % gx;
+    }
   }
   step_tile<T, ROWTILE, B16, QE2, IP, SHIFT>(p, a, b, rpull, rstore, rpsi, rspull, rsstore,
                                              qtab, tile, red);
@@ -514,15 +528,51 @@ template hipError_t launch_step_batch<double>(const InstDev *, int, int, int, in
 template hipError_t launch_step_batch<float>(const InstDev *, int, int, int, int, bool, int,
                                              hipStream_t, int, int, int, bool, bool);
 
+// Whether rows that do not fill their last tile (nx % 64 != 0) are walked in
+// row tiles (idle lanes, but scalar loads of the reference values) or in flat
+// ones (64 consecutive nodes, the references gathered per lane).  `row` and
+// `flat` count the tiles, a round is what the chip holds at once (12 waves per
+// CU).  us per step, flat / row tiles:
+//   BF16 NQ 16   300 x 500 1630 / 1050   500 x 300 1625 / 1060  1000 x 150 1600 / 1050
+//                100 x 1500 1650 / 1070  90 x 1666 1645 / 1600 (two rounds)
+//        NQ 12   500 x 1400 2950 / 2100 1000 x 700 2900 / 2220  200 x 3500 2850 / 3140 (28 % idle)
+//        NQ 8    500 x 80     88 / 59    200 x 200   86 / 77 (two rounds)
+//   FP32 shift   300 x 500 2270 / 1790   500 x 300 2270 / 1740  1000 x 150 2285 / 1855
+//        NQ 12   500 x 1400 3810 / 4060 (many rounds: writes of partial lines)
+//        NQ 8    500 x 80    140 / 132
+//   FP32 Taylor  300 x 500 1720 / 1630   500 x 300 1700 / 1690  1000 x 150 1700 / 1690
+// FP64 has no references; in place and in groups nx is a multiple of 64.
 template <typename T>
-hipError_t launch_step(const StepParams &p, StateT<T> a, StateT<T> b,
+static bool use_row_tiles(const StepParams &p, bool b16, int ip) {
+  if (p.nx % 64 == 0) return true;
+  if (ip != 0 || p.wg != 0 || std::is_same<T, double>::value) return false;
+  const long long flat = p.ntiles, row = (long long)p.ny * ((p.nx + 63) / 64);
+  const long long round = 256 * (12 / p.qs);  // qs <= 8
+  const bool one = row <= round, few_idle = 5 * row <= 6 * flat;
+  if (b16) return few_idle ? 3 * ((row + round - 1) / round) <= 4 * ((flat + round - 1) / round)
+                           : one && 2 * row <= 3 * flat;
+  return one && few_idle && p.shift;
+}
+
+template <typename T>
+hipError_t launch_step(const StepParams &pin, StateT<T> a, StateT<T> b,
                        StepRef r, const QNode *qtab, hipStream_t s, bool b16, int ip) {
-  if (use_narrow(p.ntiles, p.qs, p.nqd) && p.wg == 0 && ip == 0)
-    return launch_step_narrow<T>(p, a, b, r, qtab, s, b16);
+  if (use_narrow(pin.ntiles, pin.qs, pin.nqd) && pin.wg == 0 && ip == 0)
+    return launch_step_narrow<T>(pin, a, b, r, qtab, s, b16);
+  if (pin.qs < 1 || pin.qs > 8) return hipErrorInvalidValue;
+  StepParams p = pin;
+  const bool rowtile = use_row_tiles<T>(p, b16, ip);
+  if (rowtile && p.nx % 64) {
+    // with one Q-slice four consecutive tiles to a workgroup, on the same
+    // Q-node together: rows start inside cache lines, which two tiles write
+    p.ntiles = p.ny * ((p.nx + 63) / 64);
+    if (p.qs == 1) p.wg = 4 | 1 << 8 | 1 << 16;
+    const int units = p.qs == 1 ? (p.ntiles + 3) / 4 : p.ntiles;
+    p.tiles_per_xcd = units >= 64 ? (units + 7) / 8 : 0;
+  }
   const int gsize = p.wg ? (p.wg & 255) * ((p.wg >> 8) & 255) : 1;
-  const int grid = p.tiles_per_xcd > 0 ? 8 * p.tiles_per_xcd : p.ntiles / gsize;
+  const int grid = p.tiles_per_xcd > 0 ? 8 * p.tiles_per_xcd : (p.ntiles + gsize - 1) / gsize;
   const size_t lds = p.qs > 1 ? (size_t)p.qs * 12 * 64 * sizeof(double) : 0;
-  const bool rowtile = (p.nx % 64) == 0;
   if (p.wg && (p.qs != 1 || !rowtile || gsize > 8)) return hipErrorInvalidValue;
   if (p.qe != 1 && p.qe != 2) return hipErrorInvalidValue;
   const dim3 g(grid), blk(64 * p.qs * gsize);
