@@ -213,25 +213,34 @@ hipError_t launch_perturb_apply(int nqd, int nx, int ny, const double *du,
                                 hipStream_t s);
 hipError_t launch_sum(const double *partial, int n, int ncomp, double *out,
                       hipStream_t s);
-hipError_t launch_amplitude_rows(int nx, int ny, const double *FLD,
-                                 double *partial, hipStream_t s);
+// A lattice as the observation passes read it: lagged psi (storage type T;
+// the FP32 form's reference [q][y]) and per-node fields of one half.
+struct ObsDev {
+  const void *PSI;
+  const double *FLD;
+  const float *refPSI;
+  int nx, ny, nqd;
+};
+// The passes below take one lattice (tab null), or a device table of nlat
+// lattices in one launch, `one` then being the largest of them.
+// Amplitude: out[lattice] = sum over rows of sum_x |U - <U>_x|^2; partial
+// holds nlat x rows doubles, rows >= every ny.
+hipError_t launch_amplitude(const ObsDev &one, const ObsDev *tab, int nlat, int rows,
+                            double *partial, double *out, hipStream_t s);
+// Diagnostics and the amplitude's sum into out[kDiagComp + 1]; partial holds
+// (kDiagFields + kObsBlocks) kDiagComp doubles, rows ny.
 template <typename T>
-hipError_t launch_diag(int nx, int ny, int nqd, const QNode *qtab,
-                       StateT<T> a, RefView ref, double *partial, int *nblocks,
-                       hipStream_t s);
-hipError_t launch_diag_final(const double *partial, int nblocks, double *out,
-                             hipStream_t s);
+hipError_t launch_diag(const ObsDev &d, const QNode *qtab, double *partial, double *rows,
+                       double *out, hipStream_t s);
 template <typename T>
-hipError_t launch_observables(int nqd, int nx, int ny, const QNode *qtab,
-                              double inv_s2, double G, double mref,
-                              StateT<T> a, RefView ref, double *out,
-                              hipStream_t s);
+hipError_t launch_observables(const ObsDev &d, const QNode *qtab, double inv_s2, double G,
+                              double mref, double *out, hipStream_t s);
 // Health of a state: out[0] = number of non-finite mixture velocities and
-// polymer densities, out[1] / out[2] = smallest / largest psi.  partial holds
-// 3 kHealthBlocks doubles.
+// polymer densities, out[1] / out[2] = smallest / largest psi, three doubles
+// per lattice.  partial holds 3 kObsBlocks doubles.
 template <typename T>
-hipError_t launch_health(int nx, int ny, int nqd, StateT<T> a, RefView ref,
-                         double *partial, double *out, hipStream_t s);
+hipError_t launch_health(const ObsDev &one, const ObsDev *tab, int nlat, double *partial,
+                         double *out, hipStream_t s);
 template <typename T>
 hipError_t launch_window(int nx, int ny, int nqd, int x0, int y0, int w, int h,
                          StateT<T> a, RefView ref, double *dst, hipStream_t s);
@@ -352,7 +361,7 @@ __device__ inline double block_max(double v, double *sh) {
 }
 
 constexpr int kDiagComp = 8;  // massS massP momx momy enstrophy psiQ2 psi minpsi
-constexpr int kDiagBlocks = 1024;   // workgroups of the diagnostics reduction
-constexpr int kHealthBlocks = 1024;  // workgroups of the health check
+constexpr int kDiagFields = 1024;  // workgroups for the diagnostics' per-node fields
+constexpr int kObsBlocks = 1024;   // most workgroups of a pass over psi
 
 }  // namespace tplk

@@ -10,6 +10,8 @@
 // value ref + deviation.
 #include "tpl_step.h"
 
+#include <algorithm>
+
 namespace tplk {
 
 // ---------------------------------------------------------------------------
@@ -1481,14 +1483,78 @@ hipError_t launch_sum(const double *partial, int n, int ncomp, double *out,
   return hipGetLastError();
 }
 
-// partial[y] = sum_x |U - <U>_x(y)|^2, one workgroup per row.
-__global__ void k_amplitude_rows(int nx, int ny, const double *__restrict__ FLD,
+// Observation of lattices (single, or every lattice of a table with
+// blockIdx.y): sums and extremes over all (r, Q)-nodes.  These passes read
+// psi once and are bound by memory for large lattices; for small ones they
+// are chains of dependent loads, so the waves share (64-node tile, Q-range)
+// items and each wave loads kObsQ Q-nodes at a time.  us, one thread per node
+// / this split: health at 64 x 64 NQ 16 64 / 10; a whole diagnostics call
+// there 78 / 33, at 72 x 72 NQ 32 268 / 37, at 1024 x 512 NQ 16 295 / 235;
+// health of 48 lattices 64 x 64 NQ 8 1400 in turn / 60 in one launch.
+constexpr int kObsQ = 8;
+constexpr int kGridY = 65535;  // lattices of one launch
+template <typename F>
+__device__ __forceinline__ void for_each_item(const ObsDev &d, int block, int blocks, F f) {
+  const int lane = threadIdx.x & 63;
+  const int wpb = blockDim.x >> 6;
+  const long long nw = (long long)blocks * wpb;
+  const long long w = (long long)block * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long long N = (long long)d.nx * d.ny, tiles = (N + 63) / 64;
+  const int parts = (d.nqd + kObsQ - 1) / kObsQ;
+  const int ranges = (int)max(1LL, min((long long)parts, nw / tiles));
+  const int len = (parts + ranges - 1) / ranges * kObsQ;
+  for (long long it = w; it < tiles * ranges; it += nw) {
+    const int range = (int)(it / tiles), q0 = range * len;
+    const long long r = (it - range * tiles) * 64 + lane;
+    if (r < N) f(r, q0, min(q0 + len, d.nqd));
+  }
+}
+// f(q, psi at node r) for q0 <= q < q1 in order, B loads in flight at a time.
+template <int B, typename T, typename F>
+__device__ __forceinline__ void for_each_psi(const ObsDev &d, long long r, int q0, int q1, F f) {
+  const long long N = (long long)d.nx * d.ny;
+  const int y = (int)(r / d.nx);
+  const T *psi = static_cast<const T *>(d.PSI);
+  auto value = [&](int q) {
+    return full(psi[(size_t)q * N + r],
+                std::is_same<T, float>::value ? (double)d.refPSI[(size_t)q * d.ny + y] : 0.0);
+  };
+  int q = q0;
+  for (; q + B <= q1; q += B) {
+    double ps[B];
+#pragma unroll
+    for (int j = 0; j < B; ++j) ps[j] = value(q + j);
+#pragma unroll
+    for (int j = 0; j < B; ++j) f(q + j, ps[j]);
+  }
+#pragma unroll 1
+  for (; q < q1; ++q) f(q, value(q));
+}
+// Grid of such a pass: one workgroup where 16 waves have an item each, else
+// workgroups of four waves, at most kObsBlocks over all lattices.
+static void obs_grid(long long N, int nqd, int nlat, unsigned &grid, unsigned &block) {
+  const long long waves = ((N + 63) / 64) * ((nqd + kObsQ - 1) / kObsQ);
+  if (waves <= 16) {
+    grid = 1;
+    block = 64 * (unsigned)waves;
+  } else {
+    const long long most = std::max(1, kObsBlocks / nlat);
+    grid = (unsigned)std::min((waves + 3) / 4, most);
+    block = 256;
+  }
+}
+
+// partial[y] = sum_x |U - <U>_x(y)|^2, one workgroup per row (of each lattice
+// of a table, rows per lattice apart).
+__global__ void k_amplitude_rows(ObsDev one, const ObsDev *__restrict__ tab, int rows,
                                  double *__restrict__ partial) {
   __shared__ double sh[16];
-  const long long N = (long long)nx * ny;
-  const int y = blockIdx.x;
-  const double *ux = FLD + (size_t)F_UX * N + (size_t)y * nx;
-  const double *uy = FLD + (size_t)F_UY * N + (size_t)y * nx;
+  const ObsDev d = tab ? tab[blockIdx.y] : one;
+  const int nx = d.nx, y = blockIdx.x;
+  if (y >= d.ny) return;
+  const long long N = (long long)nx * d.ny;
+  const double *ux = d.FLD + (size_t)F_UX * N + (size_t)y * nx;
+  const double *uy = d.FLD + (size_t)F_UY * N + (size_t)y * nx;
   double sx = 0.0, sy = 0.0;
   for (int x = threadIdx.x; x < nx; x += 256) {
     sx += ux[x];
@@ -1502,36 +1568,73 @@ __global__ void k_amplitude_rows(int nx, int ny, const double *__restrict__ FLD,
     acc += dx * dx + dy * dy;
   }
   const double t = block_sum(acc, sh);
-  if (threadIdx.x == 0) partial[y] = t;
+  if (threadIdx.x == 0) partial[(size_t)blockIdx.y * rows + y] = t;
+}
+__global__ void k_amplitude_sum(ObsDev one, const ObsDev *__restrict__ tab, int rows,
+                                const double *__restrict__ partial, double *__restrict__ out) {
+  __shared__ double sh[16];
+  const int ny = tab ? tab[blockIdx.x].ny : one.ny;
+  const double *p = partial + (size_t)blockIdx.x * rows;
+  double v = 0.0;
+  for (int i = threadIdx.x; i < ny; i += 256) v += p[i];
+  v = block_sum(v, sh);
+  if (threadIdx.x == 0) out[blockIdx.x] = v;
 }
 
-hipError_t launch_amplitude_rows(int nx, int ny, const double *FLD,
-                                 double *partial, hipStream_t s) {
-  hipLaunchKernelGGL(k_amplitude_rows, dim3(ny), dim3(256), 0, s, nx, ny, FLD,
-                     partial);
+hipError_t launch_amplitude(const ObsDev &one, const ObsDev *tab, int nlat, int rows,
+                            double *partial, double *out, hipStream_t s) {
+  if (nlat < 1 || rows < 1) return hipErrorInvalidValue;
+  for (int l = 0; l < nlat; l += kGridY) {
+    const int m = std::min(nlat - l, kGridY);
+    const ObsDev *t = tab ? tab + l : nullptr;
+    hipLaunchKernelGGL(k_amplitude_rows, dim3(rows, m), dim3(256), 0, s, one, t, rows, partial);
+    hipLaunchKernelGGL(k_amplitude_sum, dim3(m), dim3(256), 0, s, one, t, rows, partial, out + l);
+  }
   return hipGetLastError();
 }
 
-// Diagnostics, one partial per workgroup: masses, population momentum,
-// enstrophy, sum psi |Q|^2, sum psi, min psi.
+// Diagnostics, one partial per workgroup.  The first nf workgroups take the
+// nodes' own fields (masses, population momentum, enstrophy; sums that cancel,
+// so their order is fixed by the lattice alone), the others sum psi |Q|^2,
+// sum psi, min psi.
 template <typename T>
-__global__ void k_diag(int nx, int ny, int nqd, const QNode *__restrict__ qtab,
-                       StateT<T> a, RefView ref, double *__restrict__ partial) {
+__global__ void __launch_bounds__(256)
+    k_diag(ObsDev d, const QNode *__restrict__ qtab, int nf, double *__restrict__ partial) {
   __shared__ double sh[16];
-  constexpr bool F32 = std::is_same<T, float>::value;
+  const int nx = d.nx, ny = d.ny;
   const long long N = (long long)nx * ny;
-  double v[kDiagComp] = {0, 0, 0, 0, 0, 0, 0, 1e300};
-  for (long long r = (long long)blockIdx.x * 256 + threadIdx.x; r < N;
-       r += (long long)gridDim.x * 256) {
-    const double *G = a.FLD;
+  double *o = partial + (size_t)blockIdx.x * kDiagComp;
+  if ((int)blockIdx.x >= nf) {
+    double v5 = 0.0, v6 = 0.0, v7 = 1e300;
+    for_each_item(d, (int)blockIdx.x - nf, (int)gridDim.x - nf, [&](long long r, int q0, int q1) {
+      for_each_psi<kObsQ, T>(d, r, q0, q1, [&](int q, double ps) {
+        const QNode CONSTANT_AS &qn = cst(qtab)[q];
+        v5 += ps * (qn.qx * qn.qx + qn.qy * qn.qy);
+        v6 += ps;
+        v7 = fmin(v7, ps);
+      });
+    });
+    v5 = block_sum(v5, sh);
+    v6 = block_sum(v6, sh);
+    v7 = block_min(v7, sh);
+    if (threadIdx.x == 0) {
+      o[5] = v5;
+      o[6] = v6;
+      o[7] = v7;
+    }
+    return;
+  }
+  double v[5] = {0, 0, 0, 0, 0};
+  for (long long r = (long long)blockIdx.x * 256 + threadIdx.x; r < N; r += (long long)nf * 256) {
+    const double *G = d.FLD;
     v[0] += G[(size_t)F_RHOS * N + r];
     v[1] += G[(size_t)F_RHOP * N + r];
     double px = G[(size_t)F_JSX * N + r], py = G[(size_t)F_JSY * N + r];
 #pragma unroll
-    for (int d = 1; d < 9; ++d) {
-      const double m = G[(size_t)(F_M0 + d) * N + r];
-      px += C9X[d] * m;
-      py += C9Y[d] * m;
+    for (int k = 1; k < 9; ++k) {
+      const double m = G[(size_t)(F_M0 + k) * N + r];
+      px += C9X[k] * m;
+      py += C9Y[k] * m;
     }
     v[2] += px;
     v[3] += py;
@@ -1542,78 +1645,79 @@ __global__ void k_diag(int nx, int ny, int nqd, const QNode *__restrict__ qtab,
     const double w = 0.5 * (uy[(size_t)y * nx + xp] - uy[(size_t)y * nx + xm]) -
                      0.5 * (ux[(size_t)yp * nx + x] - ux[(size_t)ym * nx + x]);
     v[4] += 0.5 * w * w;
-    for (int q = 0; q < nqd; ++q) {
-      const double ps = full(a.PSI[(size_t)q * N + r], F32 ? (double)ref.PSI[(size_t)q * ny + y] : 0.0);
-      v[5] += ps * (qtab[q].qx * qtab[q].qx + qtab[q].qy * qtab[q].qy);
-      v[6] += ps;
-      v[7] = fmin(v[7], ps);
-    }
   }
-  for (int c = 0; c < kDiagComp - 1; ++c) {
+  for (int c = 0; c < 5; ++c) {
     const double t = block_sum(v[c], sh);
-    if (threadIdx.x == 0) partial[(size_t)blockIdx.x * kDiagComp + c] = t;
-  }
-  const double mn = block_min(v[7], sh);
-  if (threadIdx.x == 0) partial[(size_t)blockIdx.x * kDiagComp + 7] = mn;
-}
-
-template <typename T>
-hipError_t launch_diag(int nx, int ny, int nqd, const QNode *qtab,
-                       StateT<T> a, RefView ref, double *partial, int *nblocks,
-                       hipStream_t s) {
-  const long long N = (long long)nx * ny;
-  long long nb = (N + 255) / 256;
-  if (nb > kDiagBlocks) nb = kDiagBlocks;
-  *nblocks = (int)nb;
-  hipLaunchKernelGGL(k_diag<T>, dim3((unsigned)nb), dim3(256), 0, s, nx, ny, nqd,
-                     qtab, a, ref, partial);
-  return hipGetLastError();
-}
-template hipError_t launch_diag<double>(int, int, int, const QNode *, StateT<double>,
-                                        RefView, double *, int *, hipStream_t);
-template hipError_t launch_diag<float>(int, int, int, const QNode *, StateT<float>,
-                                       RefView, double *, int *, hipStream_t);
-
-__global__ void k_diag_final(const double *__restrict__ partial, int n,
-                             double *__restrict__ out) {
-  __shared__ double sh[16];
-  for (int c = 0; c < kDiagComp; ++c) {
-    double v = (c == kDiagComp - 1) ? 1e300 : 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) {
-      const double p = partial[(size_t)i * kDiagComp + c];
-      v = (c == kDiagComp - 1) ? fmin(v, p) : v + p;
-    }
-    const double t = (c == kDiagComp - 1) ? block_min(v, sh) : block_sum(v, sh);
-    if (threadIdx.x == 0) out[c] = t;
+    if (threadIdx.x == 0) o[c] = t;
   }
 }
 
-hipError_t launch_diag_final(const double *partial, int nblocks, double *out,
-                             hipStream_t s) {
-  hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(256), 0, s, partial, nblocks,
-                     out);
-  return hipGetLastError();
+// out[0 .. kDiagComp - 1]: the partials' sums and minimum; out[kDiagComp]:
+// the sum of the amplitude's ny row sums, in k_amplitude_sum's order.
+__global__ void k_diag_final(const double *__restrict__ partial, int nf, int n,
+                             const double *__restrict__ rows, int ny, double *__restrict__ out) {
+  __shared__ double sh[4][kDiagComp + 1];
+  double v[kDiagComp + 1] = {0, 0, 0, 0, 0, 0, 0, 1e300, 0};
+  for (int i = threadIdx.x; i < nf; i += 256)
+    for (int c = 0; c < 5; ++c) v[c] += partial[(size_t)i * kDiagComp + c];
+  for (int i = nf + threadIdx.x; i < n; i += 256) {
+    const double *p = partial + (size_t)i * kDiagComp;
+    v[5] += p[5];
+    v[6] += p[6];
+    v[7] = fmin(v[7], p[7]);
+  }
+  for (int i = threadIdx.x; i < ny; i += 256) v[8] += rows[i];
+#pragma unroll
+  for (int c = 0; c <= kDiagComp; ++c) {
+    const double t = c == kDiagComp - 1 ? wave_min(v[c]) : wave_sum(v[c]);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][c] = t;
+  }
+  __syncthreads();
+  const int c = threadIdx.x;
+  if (c <= kDiagComp) {
+    double t = sh[0][c];
+    for (int w = 1; w < 4; ++w) t = c == kDiagComp - 1 ? fmin(t, sh[w][c]) : t + sh[w][c];
+    out[c] = t;
+  }
 }
 
-// Observables: rho, Ux, Uy, rhoP, C (3), tau_p (3).
 template <typename T>
-__global__ void k_observables(int nqd, int nx, int ny, const QNode *__restrict__ qtab,
-                              double inv_s2, double G, double mref, StateT<T> a,
-                              RefView ref, double *__restrict__ out) {
-  constexpr bool F32 = std::is_same<T, float>::value;
-  const long long N = (long long)nx * ny;
+hipError_t launch_diag(const ObsDev &d, const QNode *qtab, double *partial, double *rows,
+                       double *out, hipStream_t s) {
+  const long long N = (long long)d.nx * d.ny;
+  const int nf = (int)std::min((N + 255) / 256, (long long)kDiagFields);
+  const long long waves = ((N + 63) / 64) * ((d.nqd + kObsQ - 1) / kObsQ);
+  const int n = nf + (int)std::min((waves + 3) / 4, (long long)kObsBlocks);
+  hipLaunchKernelGGL(k_diag<T>, dim3(n), dim3(256), 0, s, d, qtab, nf, partial);
+  hipLaunchKernelGGL(k_amplitude_rows, dim3(d.ny), dim3(256), 0, s, d, nullptr, d.ny, rows);
+  hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(256), 0, s, partial, nf, n, rows, d.ny, out);
+  return hipGetLastError();
+}
+template hipError_t launch_diag<double>(const ObsDev &, const QNode *, double *, double *,
+                                        double *, hipStream_t);
+template hipError_t launch_diag<float>(const ObsDev &, const QNode *, double *, double *,
+                                       double *, hipStream_t);
+
+// Observables: rho, Ux, Uy, rhoP, C (3), tau_p (3).  Each node's Q-sums run
+// in order (a chain per node), B loads of psi in flight: 16 where the waves
+// are too few to hide a load (us, one load / 16: 64 x 64 NQ 16 26 / 10, 72 x
+// 72 NQ 32 212 / 68, 500 x 300 NQ 16 85 / 41), two for large lattices (1024 x
+// 512 NQ 16, one / two / 16: 165 / 164 / 205; FP32 144 / 106 with two).
+template <typename T, int B>
+__global__ void k_observables(ObsDev d, const QNode *__restrict__ qtab, double inv_s2, double G,
+                              double mref, double *__restrict__ out) {
+  const long long N = (long long)d.nx * d.ny;
   const long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= N) return;
-  const int y = (int)(r / nx);
   double ps = 0.0, cxx = 0.0, cxy = 0.0, cyy = 0.0;
-  for (int q = 0; q < nqd; ++q) {
-    const double v = full(a.PSI[(size_t)q * N + r], F32 ? (double)ref.PSI[(size_t)q * ny + y] : 0.0);
+  for_each_psi<B, T>(d, r, 0, d.nqd, [&](int q, double v) {
+    const QNode CONSTANT_AS &qn = cst(qtab)[q];
     ps += v;
-    cxx += v * qtab[q].qx * qtab[q].qx;
-    cxy += v * qtab[q].qx * qtab[q].qy;
-    cyy += v * qtab[q].qy * qtab[q].qy;
-  }
-  const double *F = a.FLD;
+    cxx += v * qn.qx * qn.qx;
+    cxy += v * qn.qx * qn.qy;
+    cyy += v * qn.qy * qn.qy;
+  });
+  const double *F = d.FLD;
   const double cn = ps > 0.0 ? inv_s2 / ps : 0.0;
   out[0 * N + r] = F[(size_t)F_RHOS * N + r] + F[(size_t)F_RHOP * N + r];
   out[1 * N + r] = F[(size_t)F_UX * N + r];
@@ -1629,60 +1733,63 @@ __global__ void k_observables(int nqd, int nx, int ny, const QNode *__restrict__
 }
 
 template <typename T>
-hipError_t launch_observables(int nqd, int nx, int ny, const QNode *qtab,
-                              double inv_s2, double G, double mref,
-                              StateT<T> a, RefView ref, double *out,
-                              hipStream_t s) {
-  const long long N = (long long)nx * ny;
-  hipLaunchKernelGGL(k_observables<T>, dim3((unsigned)((N + 255) / 256)),
-                     dim3(256), 0, s, nqd, nx, ny, qtab, inv_s2, G, mref, a, ref, out);
+hipError_t launch_observables(const ObsDev &d, const QNode *qtab, double inv_s2, double G,
+                              double mref, double *out, hipStream_t s) {
+  const long long N = (long long)d.nx * d.ny;
+  if (N < 256 * 1024)
+    hipLaunchKernelGGL((k_observables<T, 16>), dim3((unsigned)((N + 63) / 64)), dim3(64), 0, s, d,
+                       qtab, inv_s2, G, mref, out);
+  else
+    hipLaunchKernelGGL((k_observables<T, 2>), dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s,
+                       d, qtab, inv_s2, G, mref, out);
   return hipGetLastError();
 }
-template hipError_t launch_observables<double>(int, int, int, const QNode *, double, double,
-                                               double, StateT<double>, RefView, double *,
-                                               hipStream_t);
-template hipError_t launch_observables<float>(int, int, int, const QNode *, double, double,
-                                              double, StateT<float>, RefView, double *,
-                                              hipStream_t);
+template hipError_t launch_observables<double>(const ObsDev &, const QNode *, double, double,
+                                               double, double *, hipStream_t);
+template hipError_t launch_observables<float>(const ObsDev &, const QNode *, double, double,
+                                              double, double *, hipStream_t);
 
-// Health of a state, per workgroup into partial[3 block + c]: the number of
-// non-finite mixture velocities and polymer densities (c = 0), and the
-// smallest and largest polymer density psi over all (r, Q)-nodes (c = 1, 2).
-// psi is a density of dumbbell configurations (Sec. VI.B): a run whose psi
-// goes negative beyond round-off has lost positivity.
+// Health of a state, per workgroup into partial[3 block + c] (a single
+// workgroup per lattice: into out): the number of non-finite mixture
+// velocities and polymer densities (c = 0), and the smallest and largest
+// polymer density psi over all (r, Q)-nodes (c = 1, 2).  psi is a density of
+// dumbbell configurations (Sec. VI.B): a run whose psi goes negative beyond
+// round-off has lost positivity.
 template <typename T>
-__global__ void k_health(int nx, int ny, int nqd, StateT<T> a, RefView ref,
-                         double *__restrict__ partial) {
+__global__ void k_health(ObsDev one, const ObsDev *__restrict__ tab, double *__restrict__ partial,
+                         double *__restrict__ out) {
   __shared__ double sh[16];
-  constexpr bool F32 = std::is_same<T, float>::value;
-  const long long N = (long long)nx * ny;
+  const ObsDev d = tab ? tab[blockIdx.y] : one;
+  const long long N = (long long)d.nx * d.ny;
   double bad = 0.0, mn = 1e300, mx = -1e300;
-  for (long long r = (long long)blockIdx.x * 256 + threadIdx.x; r < N;
-       r += (long long)gridDim.x * 256) {
-    const double ux = a.FLD[(size_t)F_UX * N + r], uy = a.FLD[(size_t)F_UY * N + r];
-    if (!isfinite(ux) || !isfinite(uy)) bad += 1.0;
-    const int y = (int)(r / nx);
-    for (int q = 0; q < nqd; ++q) {
-      const double ps = full(a.PSI[(size_t)q * N + r],
-                             F32 ? (double)ref.PSI[(size_t)q * ny + y] : 0.0);
+  for_each_item(d, blockIdx.x, gridDim.x, [&](long long r, int q0, int q1) {
+    if (q0 == 0) {
+      const double ux = d.FLD[(size_t)F_UX * N + r], uy = d.FLD[(size_t)F_UY * N + r];
+      if (!isfinite(ux) || !isfinite(uy)) bad += 1.0;
+    }
+    for_each_psi<kObsQ, T>(d, r, q0, q1, [&](int, double ps) {
       if (!isfinite(ps)) bad += 1.0;
       mn = fmin(mn, ps);
       mx = fmax(mx, ps);
-    }
-  }
+    });
+  });
   const double b = block_sum(bad, sh);
   const double lo = block_min(mn, sh);
   const double hi = block_max(mx, sh);
   if (threadIdx.x == 0) {
-    partial[3 * (size_t)blockIdx.x] = b;
-    partial[3 * (size_t)blockIdx.x + 1] = lo;
-    partial[3 * (size_t)blockIdx.x + 2] = hi;
+    double *o = gridDim.x == 1 ? out + 3 * (size_t)blockIdx.y
+                               : partial + 3 * ((size_t)blockIdx.y * gridDim.x + blockIdx.x);
+    o[0] = b;
+    o[1] = lo;
+    o[2] = hi;
   }
 }
 
 __global__ void k_health_final(const double *__restrict__ partial, int n,
                                double *__restrict__ out) {
   __shared__ double sh[16];
+  partial += 3 * (size_t)blockIdx.x * n;
+  out += 3 * (size_t)blockIdx.x;
   double b = 0.0, mn = 1e300, mx = -1e300;
   for (int i = threadIdx.x; i < n; i += 256) {
     b += partial[3 * (size_t)i];
@@ -1700,20 +1807,25 @@ __global__ void k_health_final(const double *__restrict__ partial, int n,
 }
 
 template <typename T>
-hipError_t launch_health(int nx, int ny, int nqd, StateT<T> a, RefView ref,
-                         double *partial, double *out, hipStream_t s) {
-  const long long N = (long long)nx * ny;
-  long long nb = (N + 255) / 256;
-  if (nb > kHealthBlocks) nb = kHealthBlocks;
-  hipLaunchKernelGGL(k_health<T>, dim3((unsigned)nb), dim3(256), 0, s, nx, ny, nqd, a, ref,
-                     partial);
-  hipLaunchKernelGGL(k_health_final, dim3(1), dim3(256), 0, s, partial, (int)nb, out);
+hipError_t launch_health(const ObsDev &one, const ObsDev *tab, int nlat, double *partial,
+                         double *out, hipStream_t s) {
+  if (nlat < 1) return hipErrorInvalidValue;
+  unsigned grid, block;
+  obs_grid((long long)one.nx * one.ny, one.nqd, nlat, grid, block);
+  for (int l = 0; l < nlat; l += kGridY) {
+    const int m = std::min(nlat - l, kGridY);
+    double *o = out + 3 * (size_t)l;
+    hipLaunchKernelGGL(k_health<T>, dim3(grid, m), dim3(block), 0, s, one,
+                       tab ? tab + l : nullptr, partial, o);
+    if (grid > 1)
+      hipLaunchKernelGGL(k_health_final, dim3(m), dim3(256), 0, s, partial, (int)grid, o);
+  }
   return hipGetLastError();
 }
-template hipError_t launch_health<double>(int, int, int, StateT<double>, RefView, double *,
-                                          double *, hipStream_t);
-template hipError_t launch_health<float>(int, int, int, StateT<float>, RefView, double *,
-                                         double *, hipStream_t);
+template hipError_t launch_health<double>(const ObsDev &, const ObsDev *, int, double *, double *,
+                                          hipStream_t);
+template hipError_t launch_health<float>(const ObsDev &, const ObsDev *, int, double *, double *,
+                                         hipStream_t);
 
 // Closed-form Hookean laminar Kolmogorov state of one column (nx = 1; one
 // workgroup per row y): the Oldroyd-B profile with the polymer populations'

@@ -4,6 +4,7 @@
 #include "tpl_internal.h"
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -957,16 +958,37 @@ int learned_source(tpl_ctx *x, int tag);  // its source for the current state (b
 namespace {
 
 // Device doubles that the diagnostics need as working memory: the
-// reduction's partials and result, then the amplitude's row sums and total.
+// reduction's partials, its result with the amplitude's sum, the row sums.
 size_t diag_scratch_doubles(int ny) {
-  return (size_t)kDiagBlocks * kDiagComp + kDiagComp + (size_t)ny + 1;
+  return (size_t)(kDiagFields + kObsBlocks) * kDiagComp + kDiagComp + (size_t)ny + 1;
+}
+
+// The current half as the observation passes read it.
+ObsDev obs_dev(const tpl_ctx *x) {
+  ObsDev d{};
+  if (fp32(x)) {
+    d.PSI = x->buf.half<float>(x->cur).PSI;
+    d.FLD = x->buf.half<float>(x->cur).FLD;
+  } else {
+    d.PSI = x->buf.half64(x->cur).PSI;
+    d.FLD = x->buf.half64(x->cur).FLD;
+  }
+  d.refPSI = ref_view(x).PSI;
+  d.nx = x->c.nx;
+  d.ny = x->c.ny;
+  d.nqd = x->d.nqd;
+  return d;
+}
+
+// The amplitude from the sum over rows.
+double amplitude_of(const tpl_ctx *x, double tot) {
+  return std::sqrt(tot / ((double)x->c.nx * x->c.ny)) / x->c.u0;
 }
 
 // A(n) with device working memory w of at least ny + 1 doubles.
 double amplitude_with(tpl_ctx *x, double *w) {
-  const int nx = x->c.nx, ny = x->c.ny;
-  if (launch_amplitude_rows(nx, ny, x->buf.half64(x->cur).FLD, w, x->stream) != hipSuccess ||
-      launch_sum(w, ny, 1, w + ny, x->stream) != hipSuccess) {
+  const int ny = x->c.ny;
+  if (launch_amplitude(obs_dev(x), nullptr, 1, ny, w, w + ny, x->stream) != hipSuccess) {
     fail(TPL_EHIP, "amplitude kernels failed");
     return NAN;
   }
@@ -976,29 +998,19 @@ double amplitude_with(tpl_ctx *x, double *w) {
     fail(TPL_EHIP, "amplitude copy failed");
     return NAN;
   }
-  return std::sqrt(tot / ((double)nx * ny)) / x->c.u0;
+  return amplitude_of(x, tot);
 }
 
 // tpl_diagnostics with device working memory w of diag_scratch_doubles(ny)
-// doubles (the BF16 form also decodes its populations into a buffer of its
-// own).
+// doubles.
 int diagnostics_with(tpl_ctx *x, double *w, tpl_diag *out) {
-  int rc;
-  int nb = 0;
-  FloatView fv;
-  if (fp32(x) && (rc = float_view(x, x->cur, fv))) return rc;
-  if (fp32(x))
-    HIPCHK(launch_diag<float>(x->c.nx, x->c.ny, x->d.nqd, x->qtab_d, fv.v, ref_view(x), w, &nb,
-                              x->stream));
-  else
-    HIPCHK(launch_diag<double>(x->c.nx, x->c.ny, x->d.nqd, x->qtab_d, x->buf.half64(x->cur),
-                               ref_view(x), w, &nb, x->stream));
-  double *res = w + (size_t)kDiagBlocks * kDiagComp;
-  HIPCHK(launch_diag_final(w, nb, res, x->stream));
-  double h[kDiagComp];
+  double *res = w + (size_t)(kDiagFields + kObsBlocks) * kDiagComp;
+  HIPCHK((fp32(x) ? launch_diag<float> : launch_diag<double>)(
+      obs_dev(x), x->qtab_d, w, res + kDiagComp + 1, res, x->stream));
+  double h[kDiagComp + 1];
   HIPCHK(hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, x->stream));
   HIPCHK(hipStreamSynchronize(x->stream));
-  const double amp = amplitude_with(x, res + kDiagComp);
+  const double amp = amplitude_of(x, h[kDiagComp]);
   out->step = (double)x->step;
   out->mass_S = h[0];
   out->mass_P = h[1];
@@ -1018,7 +1030,7 @@ int diagnostics_with(tpl_ctx *x, double *w, tpl_diag *out) {
 // nothing needs clearing); calls that overlap on one GPU race.  Host code
 // uses only its device address from noalloc_scratch(), never the name.
 constexpr int kNoAllocRows = 1 << 16;
-constexpr size_t kNoAllocDoubles = (size_t)kDiagBlocks * kDiagComp + kDiagComp + kNoAllocRows + 1;
+constexpr size_t kNoAllocDoubles = (size_t)(kDiagFields + kObsBlocks) * kDiagComp + kDiagComp + kNoAllocRows + 1;
 static __device__ __align__(256) double scratch[kNoAllocDoubles];
 
 constexpr int kMaxDevices = 64;
@@ -1093,22 +1105,6 @@ int advance(tpl_ctx *x, int64_t n) {
   return TPL_OK;
 }
 
-// Health of the current state (non-finite U or psi, min and max psi) into
-// out[3]; partial and out are device arrays (3 kHealthBlocks and 3 doubles).
-int health(tpl_ctx *x, double *partial, double *dout, hipStream_t s, double out[3]) {
-  if (fp32(x))
-    HIPCHK(launch_health<float>(x->c.nx, x->c.ny, x->d.nqd, x->buf.half<float>(x->cur),
-                                ref_view(x), partial, dout, s));
-  else
-    HIPCHK(launch_health<double>(x->c.nx, x->c.ny, x->d.nqd, x->buf.half64(x->cur),
-                                 ref_view(x), partial, dout, s));
-  if (out) {
-    HIPCHK(hipMemcpyAsync(out, dout, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-  }
-  return TPL_OK;
-}
-
 // TPL_EUNSTABLE (with the step and the cause) if the state holds NaN/Inf or
 // psi below -psi_floor max psi.
 int judge_health(const tpl_ctx *x, const double h[3]) {
@@ -1127,11 +1123,13 @@ int judge_health(const tpl_ctx *x, const double h[3]) {
 }
 
 int check_health(tpl_ctx *x) {
-  int rc = ensure_scratch(x, 3 * (size_t)kHealthBlocks + 3);
+  int rc = ensure_scratch(x, 3 * (size_t)kObsBlocks + 3);
   if (rc) return rc;
-  double h[3];
-  rc = health(x, x->scratch, x->scratch + 3 * (size_t)kHealthBlocks, x->stream, h);
-  if (rc) return rc;
+  double h[3], *res = x->scratch + 3 * (size_t)kObsBlocks;
+  HIPCHK((fp32(x) ? launch_health<float> : launch_health<double>)(obs_dev(x), nullptr, 1,
+                                                                  x->scratch, res, x->stream));
+  HIPCHK(hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, x->stream));
+  HIPCHK(hipStreamSynchronize(x->stream));
   return judge_health(x, h);
 }
 
@@ -1452,14 +1450,8 @@ int tpl_moments_device(tpl_ctx *x, void *dptr, size_t len) {
   if (!dptr || len < (size_t)TPL_NFIELDS * N) return fail(TPL_EINVAL, "output too small");
   const double s2 = x->d.sigma * x->d.sigma;
   const double G = x->d.G, mref = x->d.rhoP0 * x->d.meq;
-  if (fp32(x))
-    HIPCHK(launch_observables<float>(x->d.nqd, x->c.nx, x->c.ny, x->qtab_d, 1.0 / s2, G, mref,
-                                     x->buf.half<float>(x->cur), ref_view(x), (double *)dptr,
-                                     x->stream));
-  else
-    HIPCHK(launch_observables<double>(x->d.nqd, x->c.nx, x->c.ny, x->qtab_d, 1.0 / s2, G, mref,
-                                      x->buf.half64(x->cur), ref_view(x), (double *)dptr,
-                                      x->stream));
+  HIPCHK((fp32(x) ? launch_observables<float> : launch_observables<double>)(
+      obs_dev(x), x->qtab_d, 1.0 / s2, G, mref, (double *)dptr, x->stream));
   return TPL_OK;
 }
 
@@ -2180,26 +2172,64 @@ int capture_graph(tpl_batch *b) {
   return TPL_OK;
 }
 
+// The batch's stable instances as one table of the observation passes: which
+// instances, the table on the device, its largest lattice (waves of the pass
+// and rows are sized by it), and `doubles` of working memory.
+struct ObsTable {
+  std::vector<int> which;
+  ObsDev *dev = nullptr, largest{};
+  int rows = 0;
+  double *work = nullptr;
+};
+int batch_obs(tpl_batch *b, size_t doubles, ObsTable &t) {
+  std::vector<ObsDev> tab;
+  double most = -1.0;
+  for (size_t i = 0; i < b->inst.size(); ++i) {
+    if (b->unstable[i]) continue;
+    tab.push_back(obs_dev(b->inst[i]));
+    t.which.push_back((int)i);
+    const ObsDev &d = tab.back();
+    t.rows = std::max(t.rows, d.ny);
+    const double work = (double)d.nx * d.ny * d.nqd;
+    if (work > most) {
+      most = work;
+      t.largest = d;
+    }
+  }
+  if (tab.empty()) return TPL_OK;
+  static_assert(sizeof(ObsDev) % sizeof(double) == 0, "table in front of the working memory");
+  const size_t head = tab.size() * sizeof(ObsDev) / sizeof(double);
+  if (head + doubles > INT_MAX) return fail(TPL_ENOMEM, "batch scratch allocation failed");
+  const int rc = batch_scratch(b, (int)(head + doubles));
+  if (rc) return rc;
+  t.dev = reinterpret_cast<ObsDev *>(b->scratch);
+  t.work = b->scratch + head;
+  HIPCHK(hipMemcpyAsync(t.dev, tab.data(), tab.size() * sizeof(ObsDev), hipMemcpyHostToDevice,
+                        b->stream));
+  HIPCHK(hipStreamSynchronize(b->stream));  // tab is the caller's memory
+  return TPL_OK;
+}
+
 // Health check of every active instance (NaN/Inf in U or psi, psi below
 // -psi_floor max psi, as tpl_step judges a context); newly unstable
 // instances are flagged and dropped from the table.
 int batch_check(tpl_batch *b, int *newly) {
   *newly = 0;
   const int n = (int)b->inst.size();
-  int rc = batch_scratch(b, 3 * n);
+  ObsTable t;
+  int rc = batch_obs(b, 3 * (size_t)kObsBlocks + 3 * (size_t)n, t);
   if (rc) return rc;
-  for (int i = 0; i < n; ++i) {
-    if (b->unstable[i]) continue;
-    tpl_ctx *x = b->inst[i];
-    rc = ensure_scratch(x, 3 * (size_t)kHealthBlocks);
-    if (rc) return rc;
-    rc = health(x, x->scratch, b->scratch + 3 * i, b->stream, nullptr);
-    if (rc) return rc;
-  }
-  std::vector<double> h(3 * n, 0.0);
-  HIPCHK(hipMemcpyAsync(h.data(), b->scratch, sizeof(double) * 3 * n, hipMemcpyDeviceToHost,
+  const int m = (int)t.which.size();
+  if (m == 0) return TPL_OK;
+  double *res = t.work + 3 * (size_t)kObsBlocks;
+  HIPCHK((batch_esize(b) == 4 ? launch_health<float> : launch_health<double>)(
+      t.largest, t.dev, m, t.work, res, b->stream));
+  std::vector<double> r(3 * (size_t)m), h(3 * (size_t)n, 0.0);
+  HIPCHK(hipMemcpyAsync(r.data(), res, sizeof(double) * r.size(), hipMemcpyDeviceToHost,
                         b->stream));
   HIPCHK(hipStreamSynchronize(b->stream));
+  for (int k = 0; k < m; ++k)
+    for (int c = 0; c < 3; ++c) h[3 * (size_t)t.which[k] + c] = r[3 * (size_t)k + c];
   for (int i = 0; i < n; ++i)
     if (!b->unstable[i] && judge_health(b->inst[i], &h[3 * i]) != TPL_OK) {
       b->unstable[i] = 1;
@@ -2476,8 +2506,22 @@ int tpl_batch_amplitudes(tpl_batch *b, double *out, int n) {
   if (!b || !out) return fail(TPL_EINVAL, "null argument");
   if (!b->inited) return fail(TPL_ESTATE, "batch not initialised (call tpl_batch_init)");
   if (n < (int)b->inst.size()) return fail(TPL_EINVAL, "output too small");
+  for (size_t i = 0; i < b->inst.size(); ++i) out[i] = NAN;
+  int rows = 0;
   for (size_t i = 0; i < b->inst.size(); ++i)
-    out[i] = b->unstable[i] ? NAN : tpl_perturbation_amplitude(b->inst[i]);
+    if (!b->unstable[i]) rows = std::max(rows, b->inst[i]->c.ny);
+  const size_t m = b->inst.size();
+  ObsTable t;
+  const int rc = batch_obs(b, m * rows + m, t);
+  if (rc || t.which.empty()) return rc;
+  double *res = t.work + m * rows;
+  HIPCHK(launch_amplitude(t.largest, t.dev, (int)t.which.size(), rows, t.work, res, b->stream));
+  std::vector<double> tot(t.which.size());
+  HIPCHK(hipMemcpyAsync(tot.data(), res, sizeof(double) * tot.size(), hipMemcpyDeviceToHost,
+                        b->stream));
+  HIPCHK(hipStreamSynchronize(b->stream));
+  for (size_t k = 0; k < tot.size(); ++k)
+    out[t.which[k]] = amplitude_of(b->inst[t.which[k]], tot[k]);
   return TPL_OK;
 }
 
