@@ -111,6 +111,12 @@ template <typename T>
 hipError_t launch_step(const StepParams &p, StateT<T> a, StateT<T> b,
                        StepRef ref, const QNode *qtab, hipStream_t s, bool b16 = false,
                        int ip = 0);
+// Whether workgroups of four tiles fill the 256 CUs evenly (at most a tenth
+// of their time idle).
+inline bool fours_even(int ntiles) {
+  const long long groups = ((long long)ntiles + 3) / 4;
+  return 10 * ((groups + 255) / 256) * 256 <= 11 * groups;
+}
 // The step for few nodes (tpl_narrow.hip): bitwise launch_step with eight
 // Q-slices (p.qs == 8, no tile groups, two arrays).  It holds 16 nodes per
 // workgroup (4 for the FP64 form up to kNarrowSmall nodes, where 16 would

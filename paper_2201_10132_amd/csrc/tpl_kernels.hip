@@ -556,6 +556,14 @@ static bool use_row_tiles(const StepParams &p, bool b16, int ip) {
   return one && few_idle && p.shift;
 }
 
+// A lattice with one Q-slice and no tuned group takes four consecutive tiles
+// to a workgroup, on the same Q-node together: the tiles' overlapping reads
+// and the lines that two of them write meet in the caches.  Not where FP64
+// workgroups would spread unevenly over the CUs in a round or two.  us per
+// step, one tile / four: FP64 NQ 8 256 x 256 300 / 269 (256 groups), 250 x 260
+// 294 / 280 (254), 320 x 256 374 / 420 (320), 256 x 257 337 / 375 (257), 1000
+// x 1000 4115 / 4090; NQ 12 700 x 1000 6300 / 6200; FP32 NQ 16 500 x 300 1718
+// / 1640, 333 x 450 1958 / 1590, NQ 12 300 x 2333 4420 / 3490.
 template <typename T>
 hipError_t launch_step(const StepParams &pin, StateT<T> a, StateT<T> b,
                        StepRef r, const QNode *qtab, hipStream_t s, bool b16, int ip) {
@@ -564,18 +572,20 @@ hipError_t launch_step(const StepParams &pin, StateT<T> a, StateT<T> b,
   if (pin.qs < 1 || pin.qs > 8) return hipErrorInvalidValue;
   StepParams p = pin;
   const bool rowtile = use_row_tiles<T>(p, b16, ip);
-  if (rowtile && p.nx % 64) {
-    // with one Q-slice four consecutive tiles to a workgroup, on the same
-    // Q-node together: rows start inside cache lines, which two tiles write
-    p.ntiles = p.ny * ((p.nx + 63) / 64);
-    if (p.qs == 1) p.wg = 4 | 1 << 8 | 1 << 16;
-    const int units = p.qs == 1 ? (p.ntiles + 3) / 4 : p.ntiles;
+  if (rowtile) p.ntiles = p.ny * ((p.nx + 63) / 64);
+  if (p.wg == 0) {
+    // no tuned group: four consecutive tiles to a workgroup
+    const bool four = p.qs == 1 && (fours_even(p.ntiles) || p.ntiles >= 8192 ||
+                                    (std::is_same<T, float>::value && p.ntiles >= 2048));
+    if (four) p.wg = 4 | 1 << 8 | 1 << 16;
+    const int units = four ? (p.ntiles + 3) / 4 : p.ntiles;
     p.tiles_per_xcd = units >= 64 ? (units + 7) / 8 : 0;
   }
   const int gsize = p.wg ? (p.wg & 255) * ((p.wg >> 8) & 255) : 1;
   const int grid = p.tiles_per_xcd > 0 ? 8 * p.tiles_per_xcd : (p.ntiles + gsize - 1) / gsize;
   const size_t lds = p.qs > 1 ? (size_t)p.qs * 12 * 64 * sizeof(double) : 0;
-  if (p.wg && (p.qs != 1 || !rowtile || gsize > 8)) return hipErrorInvalidValue;
+  if (p.wg && (p.qs != 1 || gsize > 8 || (!rowtile && (p.wg >> 8 & 255) != 1)))
+    return hipErrorInvalidValue;
   if (p.qe != 1 && p.qe != 2) return hipErrorInvalidValue;
   const dim3 g(grid), blk(64 * p.qs * gsize);
 #define TPL_STEP_ARGS p, a, b, r.pull, r.store, r.psi, r.spull, r.sstore, qtab

@@ -318,6 +318,10 @@ StepParams make_step_params(const tpl_ctx *x, int nx, int ny, int qs_req) {
   if (qs <= 0) {  // aim at >= 2048 waves in flight, at most 8 slices
     qs = 1;
     while (qs < 8 && (long long)p.ntiles * qs < 2048) qs *= 2;
+    // FP64: one slice where workgroups of four tiles take every CU once (us
+    // per step, two slices / one in fours: 256 x 256 NQ 8 306 / 269, NQ 16 1240
+    // / 1088; the FP32 and BF16 forms keep the order of their sums)
+    if (qs == 2 && x->c.precision == TPL_FP64 && fours_even(p.ntiles)) qs = 1;
   }
   // in place, every wave owns its nodes' populations: one Q-slice
   if (x->c.inplace && nx == x->c.nx && ny == x->c.ny) qs = 1;
@@ -563,6 +567,8 @@ int tune_groups(tpl_ctx *x) {
   x->wg_tuned = 0;
   StepParams p0 = make_step_params(x, x->c.nx, x->c.ny, x->c.qsplit);
   if (p0.qs != 1 || p0.wg != 0 || x->c.group_x * x->c.group_y > 1) return TPL_OK;
+  // one round of workgroups: groups of four, the launch's own choice, are best
+  if (x->c.qsplit <= 0 && p0.ntiles < 2048) return TPL_OK;
   const Buffers &B = x->buf;
   const bool b16 = B.xsize == 2;
   const auto &cand = kTuneCand;

@@ -1,6 +1,7 @@
-"""Rows that do not fill their last 64-node tile: a state that repeats along x
-stays so bit for bit, so the ragged lattice and several of it side by side,
-whose rows fill their tiles, must agree bitwise."""
+"""Rows that do not fill their last 64-node tile, and workgroups of four
+consecutive tiles: a state that repeats along x stays so bit for bit, so a
+lattice and several of it side by side, which take another kernel or another
+grouping, must agree bitwise."""
 import numpy as np
 import pytest
 
@@ -18,6 +19,9 @@ CASES = [  # nx, ny, copies, precision, Q-slices, options
     (112, 6, 4, P.TPL_FP32, 1, dict(spring_shift=1)),
     (112, 6, 4, P.TPL_FP32, 4, dict(spring_shift=1)),
     (80, 6, 4, P.TPL_FP32, 1, dict(spring_shift=1)),      # flat: too many idle lanes
+    (85, 253, 3, P.TPL_FP64, 1, dict(nq=4, periods=2)),   # 337 tiles / 1009 in fours
+    (111, 400, 3, P.TPL_FP32, 1, dict(nq=4, periods=4)),  # 694 tiles / 2082 in fours
+    (64, 255, 4, P.TPL_FP64, 1, dict(nq=4, periods=2, inplace=1)),  # 255 / 1020
 ]
 
 
@@ -33,8 +37,8 @@ def test_ragged_rows_are_bitwise_whole_rows(nx, ny, rep, precision, qs, option):
     st = one.get_state()
     one.set_state(**st)
     many.set_state(**{k: np.tile(v, (1,) * (v.ndim - 1) + (rep,)) for k, v in st.items()})
-    one.step(5)
-    many.step(5)
+    one.step(6)
+    many.step(6)
     a, b = one.get_state(), many.get_state()
     for k in a:
         assert np.array_equal(np.tile(a[k], (1,) * (a[k].ndim - 1) + (rep,)), b[k]), k
