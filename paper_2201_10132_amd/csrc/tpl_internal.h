@@ -243,7 +243,7 @@ hipError_t launch_observables(const ObsDev &d, const QNode *qtab, double inv_s2,
                               double mref, double *out, hipStream_t s);
 // Health of a state: out[0] = number of non-finite mixture velocities and
 // polymer densities, out[1] / out[2] = smallest / largest psi, three doubles
-// per lattice.  partial holds 3 kObsBlocks doubles.
+// per lattice.  partial holds 3 kObsBlocks doubles, 3 kObsTable with a table.
 template <typename T>
 hipError_t launch_health(const ObsDev &one, const ObsDev *tab, int nlat, double *partial,
                          double *out, hipStream_t s);
@@ -369,5 +369,6 @@ __device__ inline double block_max(double v, double *sh) {
 constexpr int kDiagComp = 8;  // massS massP momx momy enstrophy psiQ2 psi minpsi
 constexpr int kDiagFields = 1024;  // workgroups for the diagnostics' per-node fields
 constexpr int kObsBlocks = 1024;   // most workgroups of a pass over psi
+constexpr int kObsTable = 4096;    // and over a table of lattices
 
 }  // namespace tplk

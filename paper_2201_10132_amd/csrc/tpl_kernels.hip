@@ -1541,14 +1541,14 @@ __device__ __forceinline__ void for_each_psi(const ObsDev &d, long long r, int q
   for (; q < q1; ++q) f(q, value(q));
 }
 // Grid of such a pass: one workgroup where 16 waves have an item each, else
-// workgroups of four waves, at most kObsBlocks over all lattices.
+// workgroups of four waves, at most kObsBlocks (kObsTable over a table).
 static void obs_grid(long long N, int nqd, int nlat, unsigned &grid, unsigned &block) {
   const long long waves = ((N + 63) / 64) * ((nqd + kObsQ - 1) / kObsQ);
   if (waves <= 16) {
     grid = 1;
     block = 64 * (unsigned)waves;
   } else {
-    const long long most = std::max(1, kObsBlocks / nlat);
+    const long long most = nlat == 1 ? kObsBlocks : std::max(1, kObsTable / nlat);
     grid = (unsigned)std::min((waves + 3) / 4, most);
     block = 256;
   }

@@ -2223,11 +2223,11 @@ int batch_check(tpl_batch *b, int *newly) {
   *newly = 0;
   const int n = (int)b->inst.size();
   ObsTable t;
-  int rc = batch_obs(b, 3 * (size_t)kObsBlocks + 3 * (size_t)n, t);
+  int rc = batch_obs(b, 3 * (size_t)kObsTable + 3 * (size_t)n, t);
   if (rc) return rc;
   const int m = (int)t.which.size();
   if (m == 0) return TPL_OK;
-  double *res = t.work + 3 * (size_t)kObsBlocks;
+  double *res = t.work + 3 * (size_t)kObsTable;
   HIPCHK((batch_esize(b) == 4 ? launch_health<float> : launch_health<double>)(
       t.largest, t.dev, m, t.work, res, b->stream));
   std::vector<double> r(3 * (size_t)m), h(3 * (size_t)n, 0.0);
