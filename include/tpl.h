@@ -442,7 +442,7 @@ int tpl_mlp_set_params(tpl_mlp *m, const float *host, size_t n);
 int tpl_mlp_set_norm(tpl_mlp *m, const float *in_mean, const float *in_std,
                      const float *out_mean, const float *out_std);
 /* Y[n][out] = network(X[n][in]) in physical units.  X and Y are device
- * pointers (FP32); synchronises before returning. */
+ * pointers (FP32) and may overlap; synchronises before returning. */
 int tpl_mlp_forward(tpl_mlp *m, const float *X, float *Y, int64_t n);
 /* Gradients of the loss over the n rows of X and T (device, FP32, T raw
  * targets [n][out]) into the host array dW (nparams floats, the flat layout);

@@ -2573,6 +2573,8 @@ struct tpl_mlp {
   uint16_t *wb = nullptr;              // W1b | W2b | W3b | W2Tb | W3Tb
   float *fb = nullptr;                 // b1[64] b2[64] b3[16] | norm (160)
   float *partial = nullptr;
+  float *stage = nullptr;  // outputs of a forward pass whose X and Y overlap
+  size_t stage_n = 0;
   int t = 0;  // Adam steps taken
 };
 
@@ -2623,6 +2625,20 @@ int mlp_ready(tpl_mlp *m) {
   m->on_device = true;
   HIPCHK(launch_mlp_pack(m->theta, m->nin, m->nout, mlp_dev(m), m->stream));
   HIPCHK(hipStreamSynchronize(m->stream));
+  return TPL_OK;
+}
+
+int mlp_stage(tpl_mlp *m, size_t n) {
+  if (n <= m->stage_n) return TPL_OK;
+  if (m->stage) HIPCHK(hipFree(m->stage));
+  m->stage = nullptr;
+  m->stage_n = 0;
+  if (hipMalloc(&m->stage, n * sizeof(float)) != hipSuccess) {
+    (void)hipGetLastError();
+    m->stage = nullptr;
+    return fail(TPL_ENOMEM, "output staging allocation failed");
+  }
+  m->stage_n = n;
   return TPL_OK;
 }
 
@@ -2800,9 +2816,17 @@ int tpl_mlp_forward(tpl_mlp *m, const float *X, float *Y, int64_t n) {
   if (!m || (n > 0 && (!X || !Y))) return fail(TPL_EINVAL, "null argument");
   if (n < 0) return fail(TPL_EINVAL, "n must be >= 0");
   if (n == 0) return TPL_OK;
-  const int rc = mlp_ready(m);
+  int rc = mlp_ready(m);
   if (rc) return rc;
-  HIPCHK(launch_mlp_forward(mlp_dev(m), mlp_in_mean(m), mlp_in_std(m), X, n, Y, m->stream));
+  // the pass reads X and writes Y in one launch: where they overlap, through
+  // a buffer of its own
+  const size_t ny = (size_t)n * m->nout * sizeof(float), nx = (size_t)n * m->nin * sizeof(float);
+  const uintptr_t x = (uintptr_t)X, y = (uintptr_t)Y;
+  const bool overlap = x < y + ny && y < x + nx;
+  if (overlap && (rc = mlp_stage(m, (size_t)n * m->nout))) return rc;
+  HIPCHK(launch_mlp_forward(mlp_dev(m), mlp_in_mean(m), mlp_in_std(m), X, n,
+                            overlap ? m->stage : Y, m->stream));
+  if (overlap) HIPCHK(hipMemcpyAsync(Y, m->stage, ny, hipMemcpyDeviceToDevice, m->stream));
   HIPCHK(hipStreamSynchronize(m->stream));
   return TPL_OK;
 }
@@ -2851,6 +2875,7 @@ void tpl_mlp_destroy(tpl_mlp *m) {
   (void)hipFree(m->wb);
   (void)hipFree(m->fb);
   (void)hipFree(m->partial);
+  (void)hipFree(m->stage);
   delete m;
 }
 
