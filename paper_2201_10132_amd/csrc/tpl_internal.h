@@ -266,7 +266,7 @@ struct MlpDev {
   const float *out_mean, *out_std;
   int nin, nout;
 };
-// Floats of one workgroup's gradient record (see k_mlp_train), and the most
+// Doubles of one workgroup's gradient record (see k_mlp_train), and the most
 // workgroups of a training pass (one per CU).
 constexpr int kMlpRecord = 4096 + 64 + 4096 + 64 + 1024 + 16 + 1;
 constexpr int kMlpRecs = 256;
@@ -278,10 +278,10 @@ hipError_t launch_mlp_forward(const MlpDev &w, const float *mean, const float *s
                               const float *X, long long n, float *Y, hipStream_t s);
 int mlp_records(long long n);
 hipError_t launch_mlp_train(const MlpDev &w, const float *mean, const float *stdv, const float *X,
-                            const float *T, long long n, float *partial, hipStream_t s);
-hipError_t launch_mlp_reduce(const float *partial, long long n, const MlpDev &w, float *grad,
+                            const float *T, long long n, double *partial, hipStream_t s);
+hipError_t launch_mlp_reduce(const double *partial, long long n, const MlpDev &w, float *grad,
                              hipStream_t s);
-hipError_t launch_mlp_update(const float *partial, long long n, const MlpDev &w, float *grad,
+hipError_t launch_mlp_update(const double *partial, long long n, const MlpDev &w, float *grad,
                              float *theta, float *m, float *v, float lr, int t, hipStream_t s);
 hipError_t launch_mlp_pack(const float *theta, int nin, int nout, const MlpDev &w,
                            hipStream_t s);

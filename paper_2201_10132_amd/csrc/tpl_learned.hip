@@ -180,23 +180,29 @@ __global__ void __launch_bounds__(256)
 // stages the operands of the weight gradients transposed (units x the chunk's
 // 128 nodes, BF16) in the workgroup's LDS; the 36 16 x 16 blocks of dW1, dW2
 // and dW3 are then shared out over the waves, each contracted over all 128
-// nodes and accumulated in its wave's registers.  Gradients of
-// loss = mean over nodes and outputs of (y - t)^2 (standardised targets); at
-// the end the workgroup writes its record to partial[]:
+// nodes.  Gradients of loss = mean over nodes and outputs of (y - t)^2
+// (standardised targets) go to the workgroup's record in partial[]:
 //   dW1 [64][64] | db1 [64] | dW2 [64][64] | db2 [64] | dW3 [16][64] |
-//   db3 [16] | sum of squared errors [1]         (kMlpRecord floats)
+//   db3 [16] | sum of squared errors [1]         (kMlpRecord doubles)
+//
+// Sums over nodes are FP32 inside the matrix cores and FP64 from run to run
+// (a finished run is added to the record in memory: the registers cannot hold
+// FP64 blocks).  A run is never longer than the share of one of 512 waves that
+// walk the tiles alone: RUN tiles of a chunk, or with RUN = 0 `chunks` chunks.
 //
 // What bounds it: the vector ALUs (32 erf and 32 exp per lane and tile against
 // 92 matrix instructions), so every SIMD should have two waves; a wave that
 // holds all 36 blocks (144 accumulators) and walks tiles alone leaves one wave
 // on every second SIMD.  65536 rows: 108 us that way, with a launch before it
-// that wrote the standardised inputs (10 us), against 55 here.
+// that wrote the standardised inputs (10 us), against 66 here (58 with sums in
+// FP32 over all of a workgroup's chunks).
 constexpr int kTrainWaves = 8, kTrainNodes = 16 * kTrainWaves;
 constexpr int kTrainStride = kTrainNodes + 8;  // LDS rows: 16 units of a read fall in 16 bank groups
+template <int RUN>
 __global__ void __launch_bounds__(64 * kTrainWaves)
     k_mlp_train(MlpDev w, const float *__restrict__ mean, const float *__restrict__ stdv,
                 const float *__restrict__ X, const float *__restrict__ T, long long n, float scale,
-                float *__restrict__ partial) {
+                int chunks, double *__restrict__ partial) {
   // rows: X 0, H1 64, H2 128, dZ1 192, dZ2 256, dY 320
   __shared__ __align__(16) uint16_t st[336][kTrainStride];
   __shared__ float red[kTrainWaves][64 + 64 + 16 + 1];
@@ -204,9 +210,13 @@ __global__ void __launch_bounds__(64 * kTrainWaves)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // weight-gradient blocks wave, wave + 8, ...: 0-15 dW1, 16-31 dW2, 32-35 dW3
   constexpr int NB = (36 + kTrainWaves - 1) / kTrainWaves;
-  v4f gW[NB];
+  double *rec = partial + (size_t)blockIdx.x * kMlpRecord;
+  double *pW1 = rec, *pb1 = pW1 + 4096, *pW2 = pb1 + 64, *pb2 = pW2 + 4096, *pW3 = pb2 + 64,
+         *pb3 = pW3 + 1024, *psse = pb3 + 16;
+  constexpr bool LONG = RUN == 0;
+  v4f held[LONG ? NB : 1];  // the chunks that the record does not have yet
 #pragma unroll
-  for (int j = 0; j < NB; ++j) gW[j] = v4f{0, 0, 0, 0};
+  for (v4f &h : held) h = v4f{0, 0, 0, 0};
   v4f gb1[4], gb2[4], gb3 = {0, 0, 0, 0};
 #pragma unroll
   for (int a = 0; a < 4; ++a) gb1[a] = gb2[a] = v4f{0, 0, 0, 0};
@@ -214,6 +224,8 @@ __global__ void __launch_bounds__(64 * kTrainWaves)
   InNorm nm;
   load_norm(mean, stdv, w.nin, g, nm);
   const long long nchunks = (n + kTrainNodes - 1) / kTrainNodes;
+  int left = chunks;  // LONG: until the run's end
+  bool first = true;  // the record is empty
   for (long long chunk = blockIdx.x; chunk < nchunks; chunk += gridDim.x) {
     const int col = 16 * wave + c;  // the node's column of the staging rows
     const long long node = chunk * kTrainNodes + col;
@@ -269,16 +281,39 @@ __global__ void __launch_bounds__(64 * kTrainWaves)
     }
     __syncthreads();
     // dW1 += dZ1^T X, dW2 += dZ2^T H1, dW3 += dY^T H2 (K = the chunk's nodes)
+    const bool put = !LONG || --left == 0 || chunk + gridDim.x >= nchunks;
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const int b = wave + kTrainWaves * j;  // wave-uniform
       if (b < 36) {
         const int ra = b < 16 ? 192 + 16 * (b >> 2) : b < 32 ? 256 + 16 * ((b - 16) >> 2) : 320;
         const int rb = b < 16 ? 16 * (b & 3) : b < 32 ? 64 + 16 * (b & 3) : 128 + 16 * (b & 3);
+        double sum[4] = {0.0, 0.0, 0.0, 0.0};
+        v4f acc = LONG ? held[LONG ? j : 0] : v4f{0, 0, 0, 0};
 #pragma unroll
-        for (int kb = 0; kb < kTrainNodes / 16; ++kb)
-          gW[j] = mfma(ld4(&st[ra + c][16 * kb + 4 * g]), ld4(&st[rb + c][16 * kb + 4 * g]), gW[j]);
+        for (int kb = 0; kb < kTrainNodes / 16; ++kb) {
+          acc = mfma(ld4(&st[ra + c][16 * kb + 4 * g]), ld4(&st[rb + c][16 * kb + 4 * g]), acc);
+          if (kb == kTrainNodes / 16 - 1 ? put : !LONG && (kb + 1) % (LONG ? 1 : RUN) == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sum[i] += acc[i];
+            acc = v4f{0, 0, 0, 0};
+          }
+        }
+        if (LONG) held[LONG ? j : 0] = acc;
+        if (put) {
+          double *dst = b < 16 ? pW1 : b < 32 ? pW2 : pW3;
+          const int mo = b < 32 ? (b & 15) >> 2 : 0, mi = b & 3;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            double &r = dst[(16 * mo + 4 * g + i) * 64 + 16 * mi + c];
+            r = first ? sum[i] : r + sum[i];
+          }
+        }
       }
+    }
+    if (put) {
+      left = chunks;
+      first = false;
     }
     __syncthreads();  // the next chunk overwrites the staging rows
   }
@@ -310,25 +345,12 @@ __global__ void __launch_bounds__(64 * kTrainWaves)
     if (g == 0) red[wave][144] = sse;
   }
   __syncthreads();
-  float *rec = partial + (size_t)blockIdx.x * kMlpRecord;
-  float *pW1 = rec, *pb1 = pW1 + 4096, *pW2 = pb1 + 64, *pb2 = pW2 + 4096, *pW3 = pb2 + 64,
-        *pb3 = pW3 + 1024, *psse = pb3 + 16;
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const int b = wave + kTrainWaves * j;
-    if (b < 36) {
-      float *dst = b < 16 ? pW1 : b < 32 ? pW2 : pW3;
-      const int mo = b < 32 ? (b & 15) >> 2 : 0, mi = b & 3;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) dst[(16 * mo + 4 * g + i) * 64 + 16 * mi + c] = gW[j][i];
-    }
-  }
   if (threadIdx.x < 145) {
     const int j = threadIdx.x;
     double s = 0.0;
     for (int v = 0; v < kTrainWaves; ++v) s += red[v][j];
-    float *dst = j < 64 ? pb1 + j : j < 128 ? pb2 + j - 64 : j < 144 ? pb3 + j - 128 : psse;
-    *dst = (float)s;
+    double *dst = j < 64 ? pb1 + j : j < 128 ? pb2 + j - 64 : j < 144 ? pb3 + j - 128 : psse;
+    *dst = s;
   }
 }
 
@@ -384,10 +406,10 @@ struct AdamStep {
 // the FP32 master parameters and renew their operand copies.  32 record
 // positions per workgroup, eight threads each: a thread that walks all the
 // records of its position alone takes 126 us for 512 of them on 37
-// workgroups, and Adam and the packing were two more launches (11 us); here 6.
+// workgroups, and Adam and the packing were two more launches (11 us); here 7.
 template <bool ADAM>
 __global__ void __launch_bounds__(256)
-    k_mlp_reduce(const float *__restrict__ partial, int nrec, MlpDev w, float *__restrict__ grad,
+    k_mlp_reduce(const double *__restrict__ partial, int nrec, MlpDev w, float *__restrict__ grad,
                  AdamStep ad) {
   __shared__ double part[8][32];
   const int jj = threadIdx.x & 31, sl = threadIdx.x >> 5;
@@ -794,21 +816,26 @@ int mlp_records(long long n) {
 }
 
 hipError_t launch_mlp_train(const MlpDev &w, const float *mean, const float *stdv, const float *X,
-                            const float *T, long long n, float *partial, hipStream_t s) {
+                            const float *T, long long n, double *partial, hipStream_t s) {
   const float scale = 2.0f / (float)((double)n * w.nout);
-  hipLaunchKernelGGL(k_mlp_train, dim3(mlp_records(n)), dim3(64 * kTrainWaves), 0, s, w, mean,
-                     stdv, X, T, n, scale, partial);
+  // a run's tiles: at most a 512th of all (rounded up)
+  const long long most = ((n + 15) / 16 + 511) / 512;
+  auto kernel = most >= 2 * kTrainWaves ? k_mlp_train<0>
+                : most >= kTrainWaves   ? k_mlp_train<kTrainWaves>
+                                        : k_mlp_train<1>;
+  hipLaunchKernelGGL(kernel, dim3(mlp_records(n)), dim3(64 * kTrainWaves), 0, s, w, mean, stdv, X,
+                     T, n, scale, (int)std::min(most / kTrainWaves, 1LL << 30), partial);
   return hipGetLastError();
 }
 
-hipError_t launch_mlp_reduce(const float *partial, long long n, const MlpDev &w, float *grad,
+hipError_t launch_mlp_reduce(const double *partial, long long n, const MlpDev &w, float *grad,
                              hipStream_t s) {
   hipLaunchKernelGGL(k_mlp_reduce<false>, dim3((kMlpRecord + 31) / 32), dim3(256), 0, s, partial,
                      mlp_records(n), w, grad, AdamStep{});
   return hipGetLastError();
 }
 
-hipError_t launch_mlp_update(const float *partial, long long n, const MlpDev &w, float *grad,
+hipError_t launch_mlp_update(const double *partial, long long n, const MlpDev &w, float *grad,
                              float *theta, float *m, float *v, float lr, int t, hipStream_t s) {
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
   const float c1 = (float)(1.0 - std::pow(0.9, t)), c2 = (float)(1.0 - std::pow(0.999, t));

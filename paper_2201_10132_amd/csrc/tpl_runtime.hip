@@ -2572,7 +2572,7 @@ struct tpl_mlp {
   float *theta = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr;  // [np] (+1: sse)
   uint16_t *wb = nullptr;              // W1b | W2b | W3b | W2Tb | W3Tb
   float *fb = nullptr;                 // b1[64] b2[64] b3[16] | norm (160)
-  float *partial = nullptr;
+  double *partial = nullptr;
   float *stage = nullptr;  // outputs of a forward pass whose X and Y overlap
   size_t stage_n = 0;
   int t = 0;  // Adam steps taken
@@ -2615,7 +2615,7 @@ int mlp_ready(tpl_mlp *m) {
   if (!alloc((void **)&m->theta, np * 4) || !alloc((void **)&m->m, np * 4) ||
       !alloc((void **)&m->v, np * 4) || !alloc((void **)&m->grad, (np + 1) * 4) ||
       !alloc((void **)&m->wb, 14336 * 2) || !alloc((void **)&m->fb, (144 + 160) * 4) ||
-      !alloc((void **)&m->partial, (size_t)kMlpRecs * kMlpRecord * 4))
+      !alloc((void **)&m->partial, (size_t)kMlpRecs * kMlpRecord * 8))
     return fail(TPL_ENOMEM, "network allocation failed");
   HIPCHK(hipMemcpyAsync(m->theta, m->theta_h.data(), np * 4, hipMemcpyHostToDevice, m->stream));
   HIPCHK(hipMemsetAsync(m->m, 0, np * 4, m->stream));
