@@ -2179,22 +2179,30 @@ int capture_graph(tpl_batch *b) {
 }
 
 // The batch's stable instances as one table of the observation passes: which
-// instances, the table on the device, its largest lattice (waves of the pass
-// and rows are sized by it), and `doubles` of working memory.
+// instances, the table on the device (null for one lattice, which the passes
+// take by value: amplitudes of a batch of one 41 us with a table, 26 without),
+// its largest lattice (waves of the pass and rows are sized by it), and
+// `doubles` of working memory.  The upload reads `tab` until the stream is next
+// synchronised, by the caller when it fetches the results.
 struct ObsTable {
   std::vector<int> which;
+  std::vector<ObsDev> tab;
   ObsDev *dev = nullptr, largest{};
   int rows = 0;
   double *work = nullptr;
+  hipStream_t stream = nullptr;
+  bool pending = false;
+  ~ObsTable() {  // after an error between the upload and the results
+    if (pending) (void)hipStreamSynchronize(stream);
+  }
 };
 int batch_obs(tpl_batch *b, size_t doubles, ObsTable &t) {
-  std::vector<ObsDev> tab;
   double most = -1.0;
   for (size_t i = 0; i < b->inst.size(); ++i) {
     if (b->unstable[i]) continue;
-    tab.push_back(obs_dev(b->inst[i]));
+    t.tab.push_back(obs_dev(b->inst[i]));
     t.which.push_back((int)i);
-    const ObsDev &d = tab.back();
+    const ObsDev &d = t.tab.back();
     t.rows = std::max(t.rows, d.ny);
     const double work = (double)d.nx * d.ny * d.nqd;
     if (work > most) {
@@ -2202,17 +2210,19 @@ int batch_obs(tpl_batch *b, size_t doubles, ObsTable &t) {
       t.largest = d;
     }
   }
-  if (tab.empty()) return TPL_OK;
+  if (t.tab.empty()) return TPL_OK;
   static_assert(sizeof(ObsDev) % sizeof(double) == 0, "table in front of the working memory");
-  const size_t head = tab.size() * sizeof(ObsDev) / sizeof(double);
+  const size_t head = t.tab.size() * sizeof(ObsDev) / sizeof(double);
   if (head + doubles > INT_MAX) return fail(TPL_ENOMEM, "batch scratch allocation failed");
   const int rc = batch_scratch(b, (int)(head + doubles));
   if (rc) return rc;
-  t.dev = reinterpret_cast<ObsDev *>(b->scratch);
   t.work = b->scratch + head;
-  HIPCHK(hipMemcpyAsync(t.dev, tab.data(), tab.size() * sizeof(ObsDev), hipMemcpyHostToDevice,
+  if (t.tab.size() == 1) return TPL_OK;
+  t.dev = reinterpret_cast<ObsDev *>(b->scratch);
+  t.stream = b->stream;
+  t.pending = true;
+  HIPCHK(hipMemcpyAsync(t.dev, t.tab.data(), t.tab.size() * sizeof(ObsDev), hipMemcpyHostToDevice,
                         b->stream));
-  HIPCHK(hipStreamSynchronize(b->stream));  // tab is the caller's memory
   return TPL_OK;
 }
 
@@ -2234,6 +2244,7 @@ int batch_check(tpl_batch *b, int *newly) {
   HIPCHK(hipMemcpyAsync(r.data(), res, sizeof(double) * r.size(), hipMemcpyDeviceToHost,
                         b->stream));
   HIPCHK(hipStreamSynchronize(b->stream));
+  t.pending = false;
   for (int k = 0; k < m; ++k)
     for (int c = 0; c < 3; ++c) h[3 * (size_t)t.which[k] + c] = r[3 * (size_t)k + c];
   for (int i = 0; i < n; ++i)
@@ -2526,6 +2537,7 @@ int tpl_batch_amplitudes(tpl_batch *b, double *out, int n) {
   HIPCHK(hipMemcpyAsync(tot.data(), res, sizeof(double) * tot.size(), hipMemcpyDeviceToHost,
                         b->stream));
   HIPCHK(hipStreamSynchronize(b->stream));
+  t.pending = false;
   for (size_t k = 0; k < tot.size(); ++k)
     out[t.which[k]] = amplitude_of(b->inst[t.which[k]], tot[k]);
   return TPL_OK;
