@@ -192,9 +192,15 @@ tpl_ctx *tpl_create(int nx, int ny, double Re, double Wi, double beta,
  *                 together; product at most 8; used with one Q-slice and
  *                 nx a multiple of 64 group_x, ny of group_y (else ignored);
  *                 a product > 1 overrides the autotuner
- *   autotune 1    1 = on the first tpl_step, time the tile-group shapes of
- *                 the full lattice (a few idempotent launches; tune_ms) and
- *                 keep the fastest; every shape gives bitwise the same step
+ *   autotune 1    1 = the library groups the tiles: four consecutive ones
+ *                 (4 x 1 with the barrier, across rows if need be) or one, by
+ *                 a rule on their number; with nx a multiple of 64 and 2048
+ *                 tiles or more (any number with qsplit 1) the first tpl_step
+ *                 also times the other shapes of the full lattice (a few
+ *                 idempotent launches; tune_ms) and keeps the fastest; every
+ *                 shape gives bitwise the same step.  0 = group_x x group_y
+ *                 tiles (1 x 1: one tile per workgroup), or a shape that was
+ *                 timed before
  *   time_kernels 0  1 = time every step-kernel launch with HIP events
  *   diag_every 0  tpl_step checks the state's health every diag_every steps
  *                 (0: once, after its last step) and stops at the first

@@ -42,10 +42,11 @@ static_assert(sizeof(QNode) == 176, "QNode layout");
 struct StepParams {
   int nx, ny, nqd, qs;  // lattice, Q-nodes, Q-slices per r-tile
   int ntiles;           // r-tiles of 64 nodes
-  int tiles_per_xcd;    // XCD-contiguous tile mapping (0 = off)
+  int tiles_per_xcd;    // XCD-contiguous tile mapping (0 = off; set at the launch)
   int y0;               // absolute row of local row 0 (forcing phase)
   int wg;               // tile groups (qs == 1 only): tiles along x in bits 0-7,
-                        // rows in bits 8-15, bit 16: barrier per Q-node; 0 = off
+                        // rows in bits 8-15, bit 16: barrier per Q-node; 0: one
+                        // tile per workgroup
   int qe;               // quasi-equilibrium model: 1 component momenta, 2 stresses
   int shift;            // spring term: 0 Taylor form, 1 psi at r +- Q/2 (interpolated)
   long long N;  // nx * ny
@@ -111,11 +112,50 @@ template <typename T>
 hipError_t launch_step(const StepParams &p, StateT<T> a, StateT<T> b,
                        StepRef ref, const QNode *qtab, hipStream_t s, bool b16 = false,
                        int ip = 0);
+// Whether rows that do not fill their last tile (nx % 64 != 0) are walked in
+// row tiles (idle lanes, but scalar loads of the reference values) or in flat
+// ones (64 consecutive nodes, the references gathered per lane).  `row` and
+// `flat` count the tiles, a round is what the chip holds at once (12 waves per
+// CU).  us per step, flat / row tiles:
+//   BF16 NQ 16   300 x 500 1630 / 1050   500 x 300 1625 / 1060  1000 x 150 1600 / 1050
+//                100 x 1500 1650 / 1070  90 x 1666 1645 / 1600 (two rounds)
+//        NQ 12   500 x 1400 2950 / 2100 1000 x 700 2900 / 2220  200 x 3500 2850 / 3140 (28 % idle)
+//        NQ 8    500 x 80     88 / 59    200 x 200   86 / 77 (two rounds)
+//   FP32 shift   300 x 500 2270 / 1790   500 x 300 2270 / 1740  1000 x 150 2285 / 1855
+//        NQ 12   500 x 1400 3810 / 4060 (many rounds: writes of partial lines)
+//        NQ 8    500 x 80    140 / 132
+//   FP32 Taylor  300 x 500 1720 / 1630   500 x 300 1700 / 1690  1000 x 150 1700 / 1690
+// FP64 has no references (f32, b16: the storage form).
+inline bool use_row_tiles(const StepParams &p, bool f32, bool b16) {
+  if (p.nx % 64 == 0) return true;
+  if (!f32) return false;
+  const long long flat = p.ntiles, row = (long long)p.ny * ((p.nx + 63) / 64);
+  const long long round = 256 * (12 / p.qs);  // qs <= 8
+  const bool one = row <= round, few_idle = 5 * row <= 6 * flat;
+  if (b16) return few_idle ? 3 * ((row + round - 1) / round) <= 4 * ((flat + round - 1) / round)
+                           : one && 2 * row <= 3 * flat;
+  return one && few_idle && p.shift;
+}
 // Whether workgroups of four tiles fill the 256 CUs evenly (at most a tenth
 // of their time idle).
 inline bool fours_even(int ntiles) {
   const long long groups = ((long long)ntiles + 3) / 4;
   return 10 * ((groups + 255) / 256) * 256 <= 11 * groups;
+}
+// StepParams::wg where neither the caller nor the tuner chose a group: with
+// one Q-slice four consecutive tiles to a workgroup, on the same Q-node
+// together: the tiles' overlapping reads and the lines that two of them write
+// meet in the caches.  Not where FP64 workgroups would spread unevenly over the
+// CUs in a round or two.  us per step, one tile / four: FP64 NQ 8 256 x 256 300
+// / 269 (256 groups), 250 x 260 294 / 280 (254), 320 x 256 374 / 420 (320), 256
+// x 257 337 / 375 (257), 1000 x 1000 4115 / 4090; NQ 12 700 x 1000 6300 / 6200;
+// FP32 NQ 16 500 x 300 1718 / 1640, 333 x 450 1958 / 1590, NQ 12 300 x 2333
+// 4420 / 3490.
+constexpr int kFours = 4 | 1 << 8 | 1 << 16;
+inline int default_group(const StepParams &p, bool f32, bool b16) {
+  if (p.qs != 1) return 0;
+  const int n = use_row_tiles(p, f32, b16) ? p.ny * ((p.nx + 63) / 64) : p.ntiles;
+  return fours_even(n) || n >= 8192 || (f32 && n >= 2048) ? kFours : 0;
 }
 // The step for few nodes (tpl_narrow.hip): bitwise launch_step with eight
 // Q-slices (p.qs == 8, no tile groups, two arrays).  It holds 16 nodes per

@@ -530,40 +530,6 @@ template hipError_t launch_step_batch<double>(const InstDev *, int, int, int, in
 template hipError_t launch_step_batch<float>(const InstDev *, int, int, int, int, bool, int,
                                              hipStream_t, int, int, int, bool, bool);
 
-// Whether rows that do not fill their last tile (nx % 64 != 0) are walked in
-// row tiles (idle lanes, but scalar loads of the reference values) or in flat
-// ones (64 consecutive nodes, the references gathered per lane).  `row` and
-// `flat` count the tiles, a round is what the chip holds at once (12 waves per
-// CU).  us per step, flat / row tiles:
-//   BF16 NQ 16   300 x 500 1630 / 1050   500 x 300 1625 / 1060  1000 x 150 1600 / 1050
-//                100 x 1500 1650 / 1070  90 x 1666 1645 / 1600 (two rounds)
-//        NQ 12   500 x 1400 2950 / 2100 1000 x 700 2900 / 2220  200 x 3500 2850 / 3140 (28 % idle)
-//        NQ 8    500 x 80     88 / 59    200 x 200   86 / 77 (two rounds)
-//   FP32 shift   300 x 500 2270 / 1790   500 x 300 2270 / 1740  1000 x 150 2285 / 1855
-//        NQ 12   500 x 1400 3810 / 4060 (many rounds: writes of partial lines)
-//        NQ 8    500 x 80    140 / 132
-//   FP32 Taylor  300 x 500 1720 / 1630   500 x 300 1700 / 1690  1000 x 150 1700 / 1690
-// FP64 has no references; in place and in groups nx is a multiple of 64.
-template <typename T>
-static bool use_row_tiles(const StepParams &p, bool b16, int ip) {
-  if (p.nx % 64 == 0) return true;
-  if (ip != 0 || p.wg != 0 || std::is_same<T, double>::value) return false;
-  const long long flat = p.ntiles, row = (long long)p.ny * ((p.nx + 63) / 64);
-  const long long round = 256 * (12 / p.qs);  // qs <= 8
-  const bool one = row <= round, few_idle = 5 * row <= 6 * flat;
-  if (b16) return few_idle ? 3 * ((row + round - 1) / round) <= 4 * ((flat + round - 1) / round)
-                           : one && 2 * row <= 3 * flat;
-  return one && few_idle && p.shift;
-}
-
-// A lattice with one Q-slice and no tuned group takes four consecutive tiles
-// to a workgroup, on the same Q-node together: the tiles' overlapping reads
-// and the lines that two of them write meet in the caches.  Not where FP64
-// workgroups would spread unevenly over the CUs in a round or two.  us per
-// step, one tile / four: FP64 NQ 8 256 x 256 300 / 269 (256 groups), 250 x 260
-// 294 / 280 (254), 320 x 256 374 / 420 (320), 256 x 257 337 / 375 (257), 1000
-// x 1000 4115 / 4090; NQ 12 700 x 1000 6300 / 6200; FP32 NQ 16 500 x 300 1718
-// / 1640, 333 x 450 1958 / 1590, NQ 12 300 x 2333 4420 / 3490.
 template <typename T>
 hipError_t launch_step(const StepParams &pin, StateT<T> a, StateT<T> b,
                        StepRef r, const QNode *qtab, hipStream_t s, bool b16, int ip) {
@@ -571,18 +537,13 @@ hipError_t launch_step(const StepParams &pin, StateT<T> a, StateT<T> b,
     return launch_step_narrow<T>(pin, a, b, r, qtab, s, b16);
   if (pin.qs < 1 || pin.qs > 8) return hipErrorInvalidValue;
   StepParams p = pin;
-  const bool rowtile = use_row_tiles<T>(p, b16, ip);
+  const bool rowtile = p.nx % 64 == 0 ||
+                       (ip == 0 && use_row_tiles(p, std::is_same<T, float>::value, b16));
   if (rowtile) p.ntiles = p.ny * ((p.nx + 63) / 64);
-  if (p.wg == 0) {
-    // no tuned group: four consecutive tiles to a workgroup
-    const bool four = p.qs == 1 && (fours_even(p.ntiles) || p.ntiles >= 8192 ||
-                                    (std::is_same<T, float>::value && p.ntiles >= 2048));
-    if (four) p.wg = 4 | 1 << 8 | 1 << 16;
-    const int units = four ? (p.ntiles + 3) / 4 : p.ntiles;
-    p.tiles_per_xcd = units >= 64 ? (units + 7) / 8 : 0;
-  }
   const int gsize = p.wg ? (p.wg & 255) * ((p.wg >> 8) & 255) : 1;
-  const int grid = p.tiles_per_xcd > 0 ? 8 * p.tiles_per_xcd : (p.ntiles + gsize - 1) / gsize;
+  const int groups = (p.ntiles + gsize - 1) / gsize;
+  p.tiles_per_xcd = groups >= 64 ? (groups + 7) / 8 : 0;
+  const int grid = p.tiles_per_xcd > 0 ? 8 * p.tiles_per_xcd : groups;
   const size_t lds = p.qs > 1 ? (size_t)p.qs * 12 * 64 * sizeof(double) : 0;
   if (p.wg && (p.qs != 1 || gsize > 8 || (!rowtile && (p.wg >> 8 & 255) != 1)))
     return hipErrorInvalidValue;

@@ -257,8 +257,8 @@ struct tpl_ctx {
   double kernel_ms = 0.0;
   long long kernel_launches = 0;
   int qs_used = 0, wg_used = 0;
-  bool tuned = false;  // tile-group shape timed (first step)
-  int wg_tuned = 0;    // its StepParams::wg (0: one tile per workgroup)
+  bool tuned = false;  // the first step has looked at the tile-group shapes
+  int wg_tuned = -1;   // the fastest's StepParams::wg (-1: none timed, default_group's)
   double tune_ms = 0.0;
   // extra body force [2][N] (a caller's field or an attached correction's)
   double *src_d = nullptr;
@@ -295,14 +295,13 @@ size_t state_elems(const tpl_ctx *x, int which) {
 // Tile groups: gx x gy tiles of 64 nodes (gy consecutive rows) per
 // workgroup, one wave each, optionally kept on the same Q-node by a barrier,
 // so that the group's overlapping stencil reads (x-shifted pulls across tile
-// edges, psi of the rows above and below) meet in the caches.  Only for one
-// Q-slice and whole tiles per row; returns false (p unchanged) otherwise.
+// edges, psi of the rows above and below) meet in the caches.  A caller's or
+// the tuner's shape is only for one Q-slice and whole tiles per row; returns
+// false (p unchanged) otherwise.
 bool set_group(StepParams &p, int gx, int gy, int sync) {
   if (p.qs != 1 || gx * gy < 2 || gx * gy > 8 || p.nx % 64 || (p.nx / 64) % gx || p.ny % gy)
     return false;
-  const int groups = p.ntiles / (gx * gy);
   p.wg = gx | (gy << 8) | (sync ? 1 << 16 : 0);
-  p.tiles_per_xcd = groups >= 64 ? (groups + 7) / 8 : 0;
   return true;
 }
 
@@ -328,16 +327,21 @@ StepParams make_step_params(const tpl_ctx *x, int nx, int ny, int qs_req) {
   // 1, 2, 4 or 8 slices (the slice reduction uses qs * 6 KB of LDS)
   qs = qs >= 8 ? 8 : qs >= 4 ? 4 : qs >= 2 ? 2 : 1;
   p.qs = qs;
-  p.tiles_per_xcd = p.ntiles >= 64 ? (p.ntiles + 7) / 8 : 0;
+  p.shift = x->c.spring_shift;
+  // the caller's group, else the tuner's, else the default's, or without the
+  // tuner one tile per workgroup
   p.wg = 0;
-  if (x->c.group_x * x->c.group_y > 1)
-    set_group(p, x->c.group_x, x->c.group_y, x->c.group_sync);
-  else if (x->tuned && nx == x->c.nx && ny == x->c.ny && x->wg_tuned)
-    set_group(p, x->wg_tuned & 255, (x->wg_tuned >> 8) & 255, (x->wg_tuned >> 16) & 1);
+  const bool set = x->c.group_x * x->c.group_y > 1 &&
+                   set_group(p, x->c.group_x, x->c.group_y, x->c.group_sync);
+  if (!set && nx == x->c.nx && ny == x->c.ny) {
+    if (qs == 1 && x->wg_tuned >= 0)
+      p.wg = x->wg_tuned;
+    else if (x->c.autotune)
+      p.wg = default_group(p, x->c.precision != TPL_FP64, x->c.precision == TPL_BF16);
+  }
   p.y0 = 0;
   const bool m2 = x->c.qe_model == 2;
   p.qe = m2 ? 2 : 1;
-  p.shift = x->c.spring_shift;
   p.tJS = m2 ? d.tau1S : d.tau2S;
   p.tJP = m2 ? d.tau1P : d.tau2P;
   p.aS = 1.0 / (2.0 * p.tJS + 1.0);
@@ -561,17 +565,29 @@ constexpr int kTuneShapes = 6;
 const int kTuneCand[kTuneShapes][3] = {{1, 1, 0}, {4, 1, 1}, {2, 2, 1},
                                        {8, 1, 0}, {8, 1, 1}, {4, 2, 1}};
 
+// The StepParams::wg to time: the default and those of kTuneCand that the
+// lattice admits (at most kTuneShapes: where fours are the default and not
+// among them, nx is no multiple of 256 and four of them are not admitted).
+std::vector<int> tune_shapes(const tpl_ctx *x, StepParams p) {
+  std::vector<int> wg{default_group(p, x->c.precision != TPL_FP64, x->c.precision == TPL_BF16)};
+  for (const auto &c : kTuneCand) {
+    p.wg = 0;
+    if (c[0] * c[1] > 1 && !set_group(p, c[0], c[1], c[2])) continue;
+    if (std::find(wg.begin(), wg.end(), p.wg) == wg.end()) wg.push_back(p.wg);
+  }
+  return wg;
+}
+
 int tune_groups(tpl_ctx *x) {
   if (x->buf.inplace) return TPL_OK;  // timed on real steps (tune_groups_inplace)
   x->tuned = true;
-  x->wg_tuned = 0;
   StepParams p0 = make_step_params(x, x->c.nx, x->c.ny, x->c.qsplit);
-  if (p0.qs != 1 || p0.wg != 0 || x->c.group_x * x->c.group_y > 1) return TPL_OK;
-  // one round of workgroups: groups of four, the launch's own choice, are best
-  if (x->c.qsplit <= 0 && p0.ntiles < 2048) return TPL_OK;
+  if (p0.qs != 1 || x->c.group_x * x->c.group_y > 1) return TPL_OK;
+  // the default group is best in one or two rounds of workgroups; of ragged
+  // rows there is no other
+  if ((x->c.qsplit <= 0 && p0.ntiles < 2048) || x->c.nx % 64) return TPL_OK;
   const Buffers &B = x->buf;
   const bool b16 = B.xsize == 2;
-  const auto &cand = kTuneCand;
   const StepRef ref =
       B.esize == 4 ? step_ref(x) : StepRef{nullptr, nullptr, nullptr, nullptr, nullptr};
   hipEvent_t e0, e1;
@@ -579,9 +595,9 @@ int tune_groups(tpl_ctx *x) {
   HIPCHK(hipEventCreate(&e1));
   float best = 0.f;
   int rc = TPL_OK;
-  for (const auto &c : cand) {
+  for (const int wg : tune_shapes(x, p0)) {
     StepParams p = p0;
-    if (c[0] * c[1] > 1 && !set_group(p, c[0], c[1], c[2])) continue;
+    p.wg = wg;
     auto launch = [&]() {
       return B.esize == 4
                  ? launch_step<float>(p, B.half<float>(x->cur), B.half<float>(1 - x->cur), ref,
@@ -619,9 +635,8 @@ constexpr int kTuneSteps = 4 * kTuneShapes;
 int tune_groups_inplace(tpl_ctx *x, long long *done) {
   *done = 0;
   x->tuned = true;
-  x->wg_tuned = 0;
   const StepParams p0 = make_step_params(x, x->c.nx, x->c.ny, x->c.qsplit);
-  if (p0.wg != 0 || x->c.group_x * x->c.group_y > 1) return TPL_OK;
+  if (x->c.group_x * x->c.group_y > 1) return TPL_OK;
   const Buffers &B = x->buf;
   const StepRef ref =
       B.esize == 4 ? step_ref(x) : StepRef{nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -629,10 +644,10 @@ int tune_groups_inplace(tpl_ctx *x, long long *done) {
   HIPCHK(hipEventCreate(&e0));
   HIPCHK(hipEventCreate(&e1));
   float best = 0.f;
-  int rc = TPL_OK, best_wg = 0;
-  for (const auto &c : kTuneCand) {
+  int rc = TPL_OK, best_wg = -1;
+  for (const int wg : tune_shapes(x, p0)) {
     StepParams p = p0;
-    if (c[0] * c[1] > 1 && !set_group(p, c[0], c[1], c[2])) continue;
+    p.wg = wg;
     auto launch = [&]() {
       const hipError_t e = enqueue_step(x, B, p, ref, x->cur, x->ip_odd ? 2 : 1);
       if (e == hipSuccess) {  // a real step

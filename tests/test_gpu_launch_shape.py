@@ -1,0 +1,60 @@
+"""The launch shape that a step reports (group_*_used, qsplit_used) is the one
+it ran in: the default's groups of four tiles, one tile per workgroup without
+the autotuner, the caller's shape, and a shape that the tuner timed; whichever
+it is, the state is bit for bit the same."""
+import numpy as np
+import pytest
+
+import paper_2201_10132_amd as P
+
+pytestmark = pytest.mark.gpu
+
+FOURS, ONE = (4, 1, 1), (0, 0, 0)
+
+
+def _run(nx, ny, precision, steps=4, **kw):
+    kw = dict(dict(periods=max(1, ny // 256), nq=4, pre_steps=10, precision=precision), **kw)
+    t = P.Tpl(nx, ny, 20.0, 0.5, 0.8, **kw)
+    t.init(seed=2, perturbation=1e-2)
+    t.step(steps)
+    used = tuple(int(t.query(k)) for k in ("group_x_used", "group_y_used", "group_sync_used"))
+    st, tune = t.get_state(), t.query("tune_ms")
+    t.close()
+    return st, used, tune
+
+
+@pytest.mark.parametrize("nx,ny,precision,option,default", [
+    (256, 256, P.TPL_FP64, {}, FOURS),                       # 256 groups
+    (192, 342, P.TPL_FP64, dict(inplace=1), ONE),            # 1026 tiles: 257 groups
+    (64, 1022, P.TPL_FP64, dict(inplace=1), FOURS),          # the last group two tiles
+    (111, 1200, P.TPL_FP32, {}, FOURS),                      # flat tiles, 2082
+    (500, 300, P.TPL_FP32, dict(spring_shift=1), FOURS),     # row tiles
+    (250, 300, P.TPL_BF16, dict(qsplit=1), ONE),             # 1200 row tiles
+    (250, 230, P.TPL_BF16, dict(qsplit=1), ONE),             # 920: 230 groups
+    (250, 255, P.TPL_BF16, dict(qsplit=1), FOURS),           # 1020
+])
+def test_default_group_is_reported(nx, ny, precision, option, default):
+    print(f"launch shape {nx}x{ny} precision {precision} {option}", flush=True)
+    ref, used, tune = _run(nx, ny, precision, autotune=0, **option)
+    assert used == ONE and tune == 0
+    st, used, tune = _run(nx, ny, precision, **option)
+    assert used == default and tune == 0
+    for k in ref:
+        assert np.array_equal(st[k], ref[k]), k
+
+
+@pytest.mark.parametrize("nx,ny,precision,option", [
+    (192, 704, P.TPL_FP32, {}),           # 2112 tiles, fours the default but no 4 x 1 group
+    (256, 544, P.TPL_FP64, dict(inplace=1)),
+])
+def test_tuned_shape_is_reported(nx, ny, precision, option):
+    print(f"tuned shape {nx}x{ny} precision {precision} {option}", flush=True)
+    ref, used, _ = _run(nx, ny, precision, steps=30, autotune=0, **option)
+    assert used == ONE
+    st, used, tune = _run(nx, ny, precision, steps=30, **option)
+    print(f"  tuned {used}, {tune:.2f} ms", flush=True)
+    assert tune > 0
+    admitted = {ONE, (2, 2, 1), FOURS} | ({(4, 2, 1)} if nx % 256 == 0 else set())
+    assert used in admitted
+    for k in ref:
+        assert np.array_equal(st[k], ref[k]), k
