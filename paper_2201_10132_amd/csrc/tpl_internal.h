@@ -144,18 +144,31 @@ inline bool fours_even(int ntiles) {
 }
 // StepParams::wg where neither the caller nor the tuner chose a group: with
 // one Q-slice four consecutive tiles to a workgroup, on the same Q-node
-// together: the tiles' overlapping reads and the lines that two of them write
-// meet in the caches.  Not where FP64 workgroups would spread unevenly over the
-// CUs in a round or two.  us per step, one tile / four: FP64 NQ 8 256 x 256 300
-// / 269 (256 groups), 250 x 260 294 / 280 (254), 320 x 256 374 / 420 (320), 256
-// x 257 337 / 375 (257), 1000 x 1000 4115 / 4090; NQ 12 700 x 1000 6300 / 6200;
-// FP32 NQ 16 500 x 300 1718 / 1640, 333 x 450 1958 / 1590, NQ 12 300 x 2333
-// 4420 / 3490.
+// together, or one.  Together the tiles' overlapping reads and the 128-byte
+// lines that two of them write meet in the caches, so fours pay most where
+// planes do not begin on lines; against them counts how unevenly they fall on
+// the CUs.  us per step, one tile / fours (the share of the CUs' time in use):
+//   even (0.9 or more): FP64 NQ 8 256 x 256 300 / 268, 250 x 260 294 / 266; NQ
+//     16 256 x 256 1182 / 1087; 320 x 256 (0.62) 374 / 420, 256 x 257 (0.50) 337 / 375
+//   FP64 from 8192 tiles: planes off lines 1030 x 1024 NQ 8 4770 / 4070, 179 x
+//     4365 3465 / 3140; on lines 1000 x 1000 3880 / 3880, 208 x 4746 3780 / 3780
+//   FP32 from 2048 tiles: whole rows 512 x 384 NQ 16 (1.0) 2010 / 1715, 640 x
+//     400 NQ 12 1405 / 1330; planes off lines 333 x 450 NQ 16 (0.76) 1937 / 1733,
+//     802 x 174 NQ 12 (0.71) 897 / 882, 395 x 509 NQ 12 (0.77) 1550 / 1300; on
+//     lines 370 x 400 NQ 12 (0.75) 792 / 860, 300 x 480 (0.73) 756 / 847, 400 x 400
+//     (0.81) 812 / 874: not there; from 8192 552 x 1580 NQ 8 1940 / 1905
+//   BF16 row tiles: 677 x 303 NQ 6 (0.81, 3333 tiles) 256 / 247, 558 x 784 NQ 8
+//     744 / 660, 200 x 700 NQ 16 (0.91) 1159 / 1033, 300 x 520 NQ 12 (0.85) 589 / 569; 282 x 465 NQ 12 (0.76, 2325) 496 / 518
+//     and 121 x 1211 (0.79, 2422) 539 / 559: from 2560; flat tiles 130 x 2636 NQ 16
+//     2690 / 2830, 87 x 6625 NQ 8 1117 / 1164: never (bound by instructions, not lines)
 constexpr int kFours = 4 | 1 << 8 | 1 << 16;
 inline int default_group(const StepParams &p, bool f32, bool b16) {
   if (p.qs != 1) return 0;
-  const int n = use_row_tiles(p, f32, b16) ? p.ny * ((p.nx + 63) / 64) : p.ntiles;
-  return fours_even(n) || n >= 8192 || (f32 && n >= 2048) ? kFours : 0;
+  const bool row = use_row_tiles(p, f32, b16);
+  const int n = row ? p.ny * ((p.nx + 63) / 64) : p.ntiles;
+  const bool lines = p.nx % 64 != 0 && p.N % 32 == 0;  // FP32 planes begin on lines
+  if (b16) return row && (fours_even(n) || n >= 2560) ? kFours : 0;
+  return fours_even(n) || n >= 8192 || (f32 && n >= 2048 && !lines) ? kFours : 0;
 }
 // The step for few nodes (tpl_narrow.hip): bitwise launch_step with eight
 // Q-slices (p.qs == 8, no tile groups, two arrays).  It holds 16 nodes per

@@ -29,6 +29,11 @@ def _run(nx, ny, precision, steps=4, **kw):
     (64, 1022, P.TPL_FP64, dict(inplace=1), FOURS),          # the last group two tiles
     (111, 1200, P.TPL_FP32, {}, FOURS),                      # flat tiles, 2082
     (500, 300, P.TPL_FP32, dict(spring_shift=1), FOURS),     # row tiles
+    (370, 400, P.TPL_FP32, {}, ONE),                         # 2313 uneven, planes on lines
+    (450, 400, P.TPL_FP32, {}, FOURS),                       # 2813, even
+    (121, 1211, P.TPL_BF16, {}, ONE),                        # 2422 row tiles, uneven
+    (200, 700, P.TPL_BF16, {}, FOURS),                       # 2800 row tiles
+    (87, 2060, P.TPL_BF16, {}, ONE),                         # 2801 flat tiles, even
     (250, 300, P.TPL_BF16, dict(qsplit=1), ONE),             # 1200 row tiles
     (250, 230, P.TPL_BF16, dict(qsplit=1), ONE),             # 920: 230 groups
     (250, 255, P.TPL_BF16, dict(qsplit=1), FOURS),           # 1020
