@@ -142,6 +142,17 @@ inline bool fours_even(int ntiles) {
   const long long groups = ((long long)ntiles + 3) / 4;
   return 10 * ((groups + 255) / 256) * 256 <= 11 * groups;
 }
+// Q-slices per tile where the caller did not choose: for at least 2048 waves in
+// flight, at most 8.
+// FP64: one slice where workgroups of four tiles take every CU once (us
+// per step, two slices / one in fours: 256 x 256 NQ 8 306 / 269, NQ 16 1240
+// / 1088; the FP32 and BF16 forms keep the order of their sums)
+inline int auto_slices(long long ntiles, bool fp64) {
+  int qs = 1;
+  while (qs < 8 && ntiles * qs < 2048) qs *= 2;
+  if (qs == 2 && fp64 && fours_even((int)ntiles)) qs = 1;
+  return qs;
+}
 // StepParams::wg where neither the caller nor the tuner chose a group: with
 // one Q-slice four consecutive tiles to a workgroup, on the same Q-node
 // together, or one.  Together the tiles' overlapping reads and the 128-byte

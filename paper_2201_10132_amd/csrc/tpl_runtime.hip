@@ -313,15 +313,7 @@ StepParams make_step_params(const tpl_ctx *x, int nx, int ny, int qs_req) {
   p.N = (long long)nx * ny;
   p.nqd = d.nqd;
   p.ntiles = (int)((p.N + 63) / 64);
-  int qs = qs_req;
-  if (qs <= 0) {  // aim at >= 2048 waves in flight, at most 8 slices
-    qs = 1;
-    while (qs < 8 && (long long)p.ntiles * qs < 2048) qs *= 2;
-    // FP64: one slice where workgroups of four tiles take every CU once (us
-    // per step, two slices / one in fours: 256 x 256 NQ 8 306 / 269, NQ 16 1240
-    // / 1088; the FP32 and BF16 forms keep the order of their sums)
-    if (qs == 2 && x->c.precision == TPL_FP64 && fours_even(p.ntiles)) qs = 1;
-  }
+  int qs = qs_req > 0 ? qs_req : auto_slices(p.ntiles, x->c.precision == TPL_FP64);
   // in place, every wave owns its nodes' populations: one Q-slice
   if (x->c.inplace && nx == x->c.nx && ny == x->c.ny) qs = 1;
   // 1, 2, 4 or 8 slices (the slice reduction uses qs * 6 KB of LDS)
@@ -2103,13 +2095,17 @@ int choose_shape_timed(tpl_batch *b) {
   int rc0 = build_main_table(b, qs_list[0]);  // sets nitems
   if (rc0) return rc0;
   if (!b->autotune) {
-    int qs = qs_list[0];
-    const int grp = b->group > 0 ? b->group : 1;
+    int qs = qs_list[0], grp = b->group > 0 ? b->group : 1;
     if (grp > 1) {
       qs = 1;
-    } else if (b->qsplit <= 0) {  // as for one lattice: >= 2048 waves, at most 8 slices
-      qs = 1;
-      while (qs < 8 && (long long)b->nitems * qs < 2048) qs *= 2;
+    } else if (b->qsplit <= 0) {
+      // one lattice as a context of its own, the same sums in the same order;
+      // the tiles of several share fewer reads, and one slice in fours loses
+      // (us per step, two slices / fours: 256 x 256 NQ 8 FP64 280 / 265, four of
+      // 128 x 128 258 / 289)
+      const bool own = b->tab.size() == 1 && batch_esize(b) == 8;
+      qs = auto_slices(b->nitems, own);
+      if (own && b->group == 0 && qs == 1 && fours_even(b->nitems)) grp = 4;
     }
     b->qs_used = qs;
     b->group_used = grp;

@@ -63,3 +63,29 @@ def test_tuned_shape_is_reported(nx, ny, precision, option):
     assert used in admitted
     for k in ref:
         assert np.array_equal(st[k], ref[k]), k
+
+
+@pytest.mark.parametrize("nx,ny,precision,qs", [
+    (128, 128, P.TPL_FP64, 8),
+    (256, 256, P.TPL_FP64, 1),
+    (256, 256, P.TPL_FP32, 2),
+    (320, 256, P.TPL_FP64, 2),
+])
+def test_batch_of_one_takes_the_slices_of_its_lattice(nx, ny, precision, qs):
+    """Without the autotuner the number of Q-slices, and with it the order of
+    the sums over Q, is that of a context of its own: the same bits."""
+    print(f"batch of one {nx}x{ny} precision {precision}", flush=True)
+    kw = dict(nq=6, pre_steps=10, autotune=0)
+    b = P.Batch([dict(nx=nx, ny=ny, Re=20.0, Wi=0.5, beta=0.8, periods=1, seed=2,
+                      perturbation=1e-2)], precision=precision, **kw)
+    b.init()
+    b.step(5)
+    t = P.Tpl(nx, ny, 20.0, 0.5, 0.8, periods=1, precision=precision, **kw)
+    t.init(seed=2, perturbation=1e-2)
+    t.step(5)
+    assert t.query("qsplit_used") == qs and b.query("qsplit_used") == qs
+    sa, sb = b.instance(0).get_state(), t.get_state()
+    for k in sa:
+        assert np.array_equal(sa[k], sb[k]), k
+    b.close()
+    t.close()
