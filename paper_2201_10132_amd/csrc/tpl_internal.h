@@ -143,14 +143,20 @@ inline bool fours_even(int ntiles) {
   return 10 * ((groups + 255) / 256) * 256 <= 11 * groups;
 }
 // Q-slices per tile where the caller did not choose: for at least 2048 waves in
-// flight, at most 8.
-// FP64: one slice where workgroups of four tiles take every CU once (us
-// per step, two slices / one in fours: 256 x 256 NQ 8 306 / 269, NQ 16 1240
-// / 1088; the FP32 and BF16 forms keep the order of their sums)
+// flight, at most 8; in FP64 one slice already where its tiles in fours fill the
+// CUs evenly in one round or two (929 to 1024 and 1861 to 2047 tiles).  us per
+// step, one slice in fours / two slices / four:
+//   NQ 8   928 tiles (232 groups)  275 / 281 / 283     960  259 / 287 / 290
+//          938 (235)               254 / 273 / 279    1024  268 / 303 / 299
+//         1860 (465)               544 / 571 / 534    1936  505 / 585 / 541
+//         2000 (500)               526 / 633 / 572    2040  550 / 643 / 600
+//   NQ 12 1016  546 / 605 / 650   1936 1080 / 1254 / 1217
+//   NQ 16  960 1056 / 1165 / 1165 1024 1088 / 1230 / 1190 2000 2029 / 2447 / 2150
+// The FP32 and BF16 forms keep the order of their sums over Q.
 inline int auto_slices(long long ntiles, bool fp64) {
+  if (fp64 && fours_even((int)ntiles)) return 1;
   int qs = 1;
   while (qs < 8 && ntiles * qs < 2048) qs *= 2;
-  if (qs == 2 && fp64 && fours_even((int)ntiles)) qs = 1;
   return qs;
 }
 // StepParams::wg where neither the caller nor the tuner chose a group: with

@@ -67,7 +67,13 @@ def test_tuned_shape_is_reported(nx, ny, precision, option):
 
 @pytest.mark.parametrize("nx,ny,precision,qs", [
     (128, 128, P.TPL_FP64, 8),
+    (256, 232, P.TPL_FP64, 4),  # 928 tiles, 232 groups of four: uneven
+    (250, 238, P.TPL_FP64, 1),  # 930
+    (250, 256, P.TPL_FP64, 1),  # 1000
     (256, 256, P.TPL_FP64, 1),
+    (256, 257, P.TPL_FP64, 2),  # 257 groups
+    (480, 248, P.TPL_FP64, 2),  # 1860, 465 groups
+    (352, 352, P.TPL_FP64, 1),  # 1936
     (256, 256, P.TPL_FP32, 2),
     (320, 256, P.TPL_FP64, 2),
 ])
