@@ -1147,7 +1147,9 @@ hipError_t launch_rest(int nqd, long long N, double rhoS0, double rhoP0,
 // Each sum runs over the Q-nodes in order; kRefreshAhead Q-nodes' loads are in
 // flight at a time.  A thread per node (every sum in one chain) is bound by
 // load latency: 1280 us at 64^2 NQ 16, 1219 on a 64-row column and 531 at
-// 256^2 NQ 8, against 64, 75 and 181 here (2.7, 0.05 and 4.0 TB/s).
+// 256^2 NQ 8, against 64, 75 and 181 here (2.7, 0.05 and 4.0 TB/s); 1024 x 512
+// NQ 16 3.4 / 2.5 ms in FP32, 3.8 / 4.2 in FP64 (5.4 TB/s; 4 Q-nodes ahead or 1,
+// tiles by XCD or pairs of tiles make no difference there).
 constexpr int kRefreshWaves = 7, kRefreshAhead = 4;
 template <typename T>
 __global__ void __launch_bounds__(64 * kRefreshWaves)
@@ -1370,9 +1372,12 @@ hipError_t launch_perturb_field(int nx, int ny, int x0, int y0, int NX, int NY,
 }
 
 // Add scale*du at first order to both species and to the lagged U: one thread
-// per (node, Q-node), those of Q-node 0 the solvent and U too.  (A thread per
-// node walking the Q-disk took 1138 us at 64^2 NQ 16 and 5995 us at 72^2
-// NQ 32, against 46 and 292 here.)
+// per (node, Q-node), those of Q-node 0 the solvent and U too.  A thread reads
+// its 25 references with its populations, before it stores: a store may alias
+// them for all the compiler knows, and each would be read again after the store
+// before (FP32 1024 x 512 NQ 16 11.9 ms so, 7.2 here; FP64 7.5).  (A thread per
+// node walking the Q-disk took 8.2 and 9.7 ms there, 1138 us at 64^2 NQ 16 and
+// 5995 us at 72^2 NQ 32, against 46 and 292 here.)
 template <typename T>
 __global__ void k_perturb_apply(int nqd, int nx, int ny, const double *__restrict__ du,
                                 const double *__restrict__ scale, StateT<T> a,
@@ -1381,7 +1386,7 @@ __global__ void k_perturb_apply(int nqd, int nx, int ny, const double *__restric
   const long long N = (long long)nx * ny;
   const long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= N) return;
-  const int y = (int)(r / nx), q = blockIdx.y;
+  const int y = (int)((uint32_t)r / (uint32_t)nx), q = blockIdx.y;
   constexpr bool F32 = std::is_same<T, float>::value;
   auto rv = [&](const float *tab, long long pl) { return F32 ? (double)tab[(size_t)pl * ny + y] : 0.0; };
   const double f = scale[0];
@@ -1403,19 +1408,23 @@ __global__ void k_perturb_apply(int nqd, int nx, int ny, const double *__restric
     a.FLD[(size_t)F_UX * N + r] += dx;
     a.FLD[(size_t)F_UY * N + r] += dy;
   }
-  double g[25], ps = 0.0;
+  T g[25];  // stored values and their references, all read before the first store
+  float rf[25];
+  double ps = 0.0;
 #pragma unroll
   for (int k = 0; k < 25; ++k) {
     const long long pl = (long long)k * nqd + q;
-    g[k] = full(a.XP[(size_t)pl * N + r], rv(ref.XP, pl));
-    ps += g[k];
+    g[k] = a.XP[(size_t)pl * N + r];
+    rf[k] = F32 ? ref.XP[(size_t)pl * ny + y] : 0.0f;
   }
+#pragma unroll
+  for (int k = 0; k < 25; ++k) ps += full(g[k], rf[k]);
 #pragma unroll
   for (int k = 0; k < 25; ++k) {
     if (PV[k][0] == 0 && PV[k][1] == 0) continue;
     const long long pl = (long long)k * nqd + q;
     a.XP[(size_t)pl * N + r] = stored<T>(
-        fma(3.0 * (1.0 / 36.0) * ps, along(PV[k][0], PV[k][1]), g[k]), rv(ref.XP, pl));
+        fma(3.0 * (1.0 / 36.0) * ps, along(PV[k][0], PV[k][1]), full(g[k], rf[k])), rf[k]);
   }
 }
 
