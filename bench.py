@@ -568,7 +568,7 @@ def kernel_source_sha() -> str:
     import hashlib
 
     h = hashlib.sha256()
-    for f in ("tpl_kernels.hip", "tpl_internal.h"):
+    for f in ("tpl_kernels.hip", "tpl_step.h", "tpl_internal.h"):
         with open(os.path.join(ROOT, "paper_2201_10132_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -26,7 +26,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 def kernel_source_sha() -> str:
     h = hashlib.sha256()
-    for f in ("tpl_kernels.hip", "tpl_internal.h"):
+    for f in ("tpl_kernels.hip", "tpl_step.h", "tpl_internal.h"):
         with open(os.path.join(ROOT, "paper_2201_10132_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
