@@ -1503,8 +1503,7 @@ int tpl_diagnostics_noalloc(tpl_ctx *x, tpl_diag *out) {
   if (rc) return rc;
   if (!out) return fail(TPL_EINVAL, "null output");
   if (bf16(x))
-    return fail(TPL_EINVAL, "tpl_diagnostics_noalloc: the BF16 form decodes into a buffer "
-                            "it would have to allocate");
+    return fail(TPL_EINVAL, "tpl_diagnostics_noalloc is for the FP64 and FP32 forms");
   if (x->c.ny > kNoAllocRows)
     return fail(TPL_EINVAL, "tpl_diagnostics_noalloc: ny = " + std::to_string(x->c.ny) +
                                 " exceeds the static working memory (at most " +
