@@ -222,9 +222,12 @@ __device__ __forceinline__ void step_tile(const StepParams &p, const StateT<T> &
       // from its two 16-bit halves (planes 0 and 25)
       // The offsets are made opaque per Q-node, or their zero extensions are
       // hoisted out of the loop and every access pays a 64-bit vector add
-      // (this form is bound by its vector instructions, 1040 per Q-node with
-      // those adds and an integer rounding, 810 without: 6.05 -> 5.5 ms per
-      // step at 1024 x 1024, NQ 16, 4.1 -> 4.5 TB/s).
+      // (this form is bound by the issue of its instructions: 565 vector, 428
+      // scalar and 57 memory ones per Q-node with those adds and an integer
+      // rounding, 480, 278 and 57 without: 6.05 -> 5.5 ms per step at 1024 x
+      // 1024, NQ 16, 4.1 -> 4.5 TB/s; 82 of the 480 widen FP32 values, most of
+      // them references that the whole wave shares, and some 250 of the 278
+      // form plane addresses).
       const char *xp = reinterpret_cast<const char *>(a.XP);
       auto hplane = [&](int i) {
         return uni(reinterpret_cast<const uint16_t *>(xp + (uint64_t)(uint32_t)i * (NT >> 1)));
